@@ -26,7 +26,7 @@
 // persistent "stream" grid when the row tiles are few and unequal), the probe
 // on attn_pos_kernel (4 waves, K/V
 // by global->LDS loads two and one tiles ahead, key positions from a table).
-// fp32 path (vector ALUs): one wave per (row, head).
+// The fp32 path is attention_f32.hip.
 #include <limits.h>
 #include <math.h>
 #include <stdlib.h>
@@ -1206,60 +1206,6 @@ __global__ __launch_bounds__(kThreads) void attn_stream_merge_kernel(
   }
 }
 
-// ---------------------------------------------------------------- fp32 path
-template <int D>
-__global__ __launch_bounds__(64) void attn_f32_kernel(
-    float* __restrict__ out, float* __restrict__ lse, const float* __restrict__ q,
-    const int32_t* __restrict__ row_pos, int64_t n_rows, const int32_t* __restrict__ cu_rows,
-    int batch, const float* __restrict__ kc, const float* __restrict__ vc, int64_t n_kv_rows,
-    int64_t kv_stride, const int32_t* __restrict__ cu_kv, const int32_t* __restrict__ kv_pos,
-    int hq, int hkv, float scale2) {
-  constexpr int E = D / 64;
-  const int64_t r = blockIdx.x;
-  const int h = blockIdx.y;
-  const int l = threadIdx.x;
-  // request of row r: last b with cu_rows[b] <= r
-  int lo = 0, hi = batch - 1;
-  while (lo < hi) {
-    const int mid = (lo + hi + 1) >> 1;
-    if (cu_rows[mid] <= r) lo = mid; else hi = mid - 1;
-  }
-  const int b = lo;
-  if (r < cu_rows[b] || r >= cu_rows[b + 1] || r >= n_rows) return;
-  const int64_t kv0 = cu_kv[b];
-  int nkv = cu_kv[b + 1] - (int)kv0;
-  if (kv0 + nkv > n_kv_rows) nkv = (int)(n_kv_rows - kv0);
-  const int g = h / (hq / hkv);
-  const int qpos = row_pos[r];
-  float qr[E], o[E];
-#pragma unroll
-  for (int e = 0; e < E; ++e) {
-    qr[e] = q[r * (int64_t)hq * D + (int64_t)h * D + l + 64 * e];
-    o[e] = 0.f;
-  }
-  float m = -INFINITY, ls = 0.f;
-  const int jend = kv_pos ? nkv : min(nkv, qpos + 1);
-  for (int j = 0; j < jend; ++j) {
-    if (kv_pos && kv_pos[kv0 + j] > qpos) continue;
-    const float* kp = kc + (kv0 + j) * kv_stride + (int64_t)g * D;
-    const float* vp = vc + (kv0 + j) * kv_stride + (int64_t)g * D;
-    float part = 0.f;
-#pragma unroll
-    for (int e = 0; e < E; ++e) part += qr[e] * kp[l + 64 * e];
-    const float x = wave_sum(part) * scale2;
-    const float mn = fmaxf(m, x);
-    const float alpha = exp2f(m - mn), p = exp2f(x - mn);
-    ls = ls * alpha + p;
-#pragma unroll
-    for (int e = 0; e < E; ++e) o[e] = o[e] * alpha + p * vp[l + 64 * e];
-    m = mn;
-  }
-  const float inv = ls > 0.f ? 1.f / ls : 0.f;
-#pragma unroll
-  for (int e = 0; e < E; ++e) out[r * (int64_t)hq * D + (int64_t)h * D + l + 64 * e] = o[e] * inv;
-  if (lse && l == 0) lse[r * hq + h] = ls > 0.f ? (m + log2f(ls)) * kLn2 : -INFINITY;
-}
-
 // Stream mode is used when the plain grid would hold fewer than 1.5 blocks per
 // CU and the row tiles fit the block's plan.  (A c3-shaped layer, 392 plain
 // blocks: plain 284 vs stream 297 us; c2, 200 blocks: plain 132 vs stream
@@ -1399,18 +1345,10 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
 #undef QCF_POS
     return hipGetLastError();
   }
-  dim3 grid((unsigned)n_rows, s.hq);
-  if (s.d == 64)
-    attn_f32_kernel<64><<<grid, 64, 0, stream>>>(
-        static_cast<float*>(out), lse, static_cast<const float*>(q), row_pos, n_rows, cu_rows,
-        s.batch, static_cast<const float*>(k_cache), static_cast<const float*>(v_cache), n_kv_rows,
-        kv_row_stride, cu_kv, kv_pos, s.hq, s.hkv, scale2);
-  else
-    attn_f32_kernel<128><<<grid, 64, 0, stream>>>(
-        static_cast<float*>(out), lse, static_cast<const float*>(q), row_pos, n_rows, cu_rows,
-        s.batch, static_cast<const float*>(k_cache), static_cast<const float*>(v_cache), n_kv_rows,
-        kv_row_stride, cu_kv, kv_pos, s.hq, s.hkv, scale2);
-  return hipGetLastError();
+  return launch_attn_f32(static_cast<float*>(out), lse, static_cast<const float*>(q), row_pos,
+                         n_rows, cu_rows, static_cast<const float*>(k_cache),
+                         static_cast<const float*>(v_cache), n_kv_rows, kv_row_stride, cu_kv,
+                         kv_pos, s, scale, stream);
 }
 
 }  // namespace qcf

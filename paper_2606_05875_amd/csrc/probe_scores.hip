@@ -24,8 +24,8 @@
 // with the same operand registers either way round: the statistics take S^T =
 // K Q^T (a lane owns one query vector, so its max and sum stay in the lane),
 // the columns take S = Q K^T (a lane owns one key, so its sum over the query
-// vectors is 16 in-lane additions and one lane swap).  The fp32 path uses the
-// vector ALUs.  Every reduction has a fixed order, so results are
+// vectors is 16 in-lane additions and one lane swap).  The fp32 path is
+// probe_scores_f32.hip.  Every reduction has a fixed order, so results are
 // deterministic.
 //
 // With a rotation table (kRot) the keys come from the stored chunk caches and
@@ -43,7 +43,7 @@
 namespace qcf {
 namespace {
 
-constexpr int kThreads = 256;      // fp32 path, final pass
+constexpr int kThreads = 256;      // final pass
 constexpr int kW = 8;              // bf16 path: waves per block
 constexpr int kQvTile = 32 * kW;   // query vectors per block
 constexpr int kChunkKeys = 128;    // keys staged in LDS at a time
@@ -359,104 +359,6 @@ __global__ __launch_bounds__(kThreads) void scores_final(float* __restrict__ sco
   scores[row] = accumulate ? scores[row] + acc : acc;
 }
 
-// ---------------------------------------------------------------- fp32 path
-// key row `row` into kr[D], turned by its rotation-table row when kRot
-template <int D, bool kRot>
-__device__ __forceinline__ void key_f32(float* kr, const float* __restrict__ kp, int64_t row,
-                                        const int32_t* __restrict__ key_rot,
-                                        const float2* __restrict__ rot_tab, int n_rot) {
-#pragma unroll
-  for (int e = 0; e < D; ++e) kr[e] = kp[e];
-  if constexpr (kRot) {
-    const float2* cs = rot_tab + (int64_t)min(max(key_rot[row], 0), n_rot - 1) * (D / 2);
-#pragma unroll
-    for (int j = 0; j < D / 2; ++j) {
-      const float x1 = kr[j], x2 = kr[j + D / 2];
-      rope_pair(x1, x2, cs[j], kr[j], kr[j + D / 2]);
-    }
-  }
-}
-
-template <int D, bool kRot>
-__global__ __launch_bounds__(64) void probe_stats_f32(float2* __restrict__ stats,
-                                                      const float* __restrict__ q, int64_t n_q_rows,
-                                                      const float* __restrict__ k, int64_t n_kv_rows,
-                                                      int64_t k_stride, const int32_t* __restrict__ key_rot,
-                                                      const float2* __restrict__ rot_tab, int n_rot,
-                                                      const int32_t* __restrict__ cu_q,
-                                                      const int32_t* __restrict__ cu_kv,
-                                                      const int32_t* __restrict__ ctx_len, int hq,
-                                                      int hkv, int max_q_len, float scale2) {
-  __shared__ float qs[D];
-  const int i = blockIdx.x, h = blockIdx.y, b = blockIdx.z;
-  const int64_t q0 = cu_q[b];
-  if (i >= cu_q[b + 1] - q0 || q0 + i >= n_q_rows) return;
-  const int g = h / (hq / hkv);
-  for (int e = threadIdx.x; e < D; e += 64) qs[e] = q[(q0 + i) * (int64_t)hq * D + (int64_t)h * D + e];
-  __syncthreads();
-  const int64_t k0 = cu_kv[b];
-  const int N = ctx_len[b];
-  float m = -INFINITY, ls = 0.f;
-  for (int t = threadIdx.x; t < N; t += 64) {
-    if (k0 + t >= n_kv_rows) break;
-    float kr[D];
-    key_f32<D, kRot>(kr, k + (k0 + t) * k_stride + (int64_t)g * D, k0 + t, key_rot, rot_tab, n_rot);
-    float acc = 0.f;
-#pragma unroll
-    for (int e = 0; e < D; ++e) acc += qs[e] * kr[e];
-    const float x = acc * scale2;
-    const float mn = fmaxf(m, x);
-    ls = ls * exp2f(m - mn) + exp2f(x - mn);
-    m = mn;
-  }
-  float2 ml = make_float2(m, ls);
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1)
-    ml = combine_ml(ml, make_float2(__shfl_xor(ml.x, o, 64), __shfl_xor(ml.y, o, 64)));
-  if (threadIdx.x == 0)
-    stats[((int64_t)b * hq + h) * max_q_len + i] = make_float2(ml.x, ml.y > 0.f ? 1.f / ml.y : 0.f);
-}
-
-template <int D, bool kRot>
-__global__ __launch_bounds__(kThreads) void probe_cols_f32(
-    float* __restrict__ scores, int accumulate, const float2* __restrict__ stats,
-    const float* __restrict__ q, int64_t n_q_rows, const float* __restrict__ k, int64_t n_kv_rows,
-    int64_t k_stride, const int32_t* __restrict__ key_rot, const float2* __restrict__ rot_tab,
-    int n_rot, const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_kv,
-    const int32_t* __restrict__ ctx_len, int hq, int hkv, int max_q_len, float scale2) {
-  const int t = blockIdx.x * kThreads + threadIdx.x;
-  const int b = blockIdx.y;
-  const int N = ctx_len[b];
-  const int64_t k0 = cu_kv[b];
-  const bool ok = t < N && k0 + t < n_kv_rows;
-  const int64_t q0 = cu_q[b];
-  const int nq = cu_q[b + 1] - (int)q0;
-  const int grp = hq / hkv;
-  float acc = 0.f;
-  float kr[D];
-  for (int h = 0; h < hq; ++h) {
-    if (h % grp == 0) {
-      const int g = h / grp;
-      if (ok)
-        key_f32<D, kRot>(kr, k + (k0 + t) * k_stride + (int64_t)g * D, k0 + t, key_rot, rot_tab, n_rot);
-      else
-#pragma unroll
-        for (int e = 0; e < D; ++e) kr[e] = 0.f;
-    }
-    for (int i = 0; i < nq && i < max_q_len; ++i) {
-      if (q0 + i >= n_q_rows) break;
-      const float* qp = q + (q0 + i) * (int64_t)hq * D + (int64_t)h * D;
-      float dot = 0.f;
-#pragma unroll
-      for (int e = 0; e < D; ++e) dot += qp[e] * kr[e];
-      const float2 ml = stats[((int64_t)b * hq + h) * max_q_len + i];
-      acc += exp2f(dot * scale2 - ml.x) * ml.y;
-    }
-  }
-  if (!ok) return;
-  scores[k0 + t] = accumulate ? scores[k0 + t] + acc : acc;
-}
-
 }  // namespace
 
 size_t probe_scores_workspace(const ProbeShape& s) {
@@ -479,43 +381,14 @@ hipError_t launch_probe_scores(float* scores, int accumulate, const void* q, int
   const float2* tab = reinterpret_cast<const float2*>(rot.table);
   const int n_rot = rt ? (int)rot.n : 1;
   if (!bf16) {
-    float2* stats = static_cast<float2*>(ws);
-    const float* qf = static_cast<const float*>(q);
-    const float* kf = static_cast<const float*>(k);
-    if (s.max_q_len > 0) {
-      dim3 g1(s.max_q_len, s.hq, s.batch);
-#define QCF_STATS(D, R)                                                                           \
-  probe_stats_f32<D, R><<<g1, 64, 0, stream>>>(stats, qf, n_q_rows, kf, n_kv_rows, k_row_stride, \
-                                               rot.row, tab, n_rot, cu_q, cu_kv, ctx_len, s.hq,  \
-                                               s.hkv, s.max_q_len, scale2)
-      if (s.d == 64) {
-        if (rt) QCF_STATS(64, true); else QCF_STATS(64, false);
-      } else {
-        if (rt) QCF_STATS(128, true); else QCF_STATS(128, false);
-      }
-#undef QCF_STATS
-    }
-    dim3 g2((s.max_ctx_len + kThreads - 1) / kThreads, s.batch);
-#define QCF_COLS(D, R)                                                                             \
-  probe_cols_f32<D, R><<<g2, kThreads, 0, stream>>>(scores, accumulate, stats, qf, n_q_rows, kf,  \
-                                                    n_kv_rows, k_row_stride, rot.row, tab, n_rot, \
-                                                    cu_q, cu_kv, ctx_len, s.hq, s.hkv,            \
-                                                    s.max_q_len, scale2)
-    if (s.d == 64) {
-      if (rt) QCF_COLS(64, true); else QCF_COLS(64, false);
-    } else {
-      if (rt) QCF_COLS(128, true); else QCF_COLS(128, false);
-    }
-#undef QCF_COLS
-    if (sel) {
-      const hipError_t e = hipGetLastError();
-      if (e != hipSuccess) return e;
-      return launch_select_topk(sel->out_idx, sel->out_pos, sel->n_out, scores, n_kv_rows,
-                                sel->n_seg, sel->seg_start, sel->seg_len, sel->seg_k,
-                                sel->out_start, nullptr, sel->max_seg_len, stream, sel->seg_req,
-                                cu_kv, s.batch);
-    }
-    return hipGetLastError();
+    const hipError_t e = launch_scores_f32(scores, accumulate, static_cast<const float*>(q), n_q_rows,
+                                           static_cast<const float*>(k), n_kv_rows, k_row_stride, rot,
+                                           cu_q, cu_kv, ctx_len, s, scale, ws, stream);
+    if (e != hipSuccess || !sel) return e;
+    return launch_select_topk(sel->out_idx, sel->out_pos, sel->n_out, scores, n_kv_rows,
+                              sel->n_seg, sel->seg_start, sel->seg_len, sel->seg_k,
+                              sel->out_start, nullptr, sel->max_seg_len, stream, sel->seg_req,
+                              cu_kv, s.batch);
   }
   const WsLayout w = ws_layout(s);
   if (s.batch > 65535) return hipErrorInvalidConfiguration;

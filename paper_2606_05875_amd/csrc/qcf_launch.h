@@ -101,6 +101,11 @@ struct KeyRot {
   int64_t n;
 };
 size_t probe_scores_workspace(const ProbeShape& s);
+hipError_t launch_scores_f32(float* scores, int accumulate, const float* q, int64_t n_q_rows,
+                             const float* k, int64_t n_kv_rows, int64_t k_row_stride,
+                             const KeyRot& rot, const int32_t* cu_q, const int32_t* cu_kv,
+                             const int32_t* ctx_len, const ProbeShape& s, float scale, void* ws,
+                             hipStream_t stream);
 hipError_t launch_probe_scores(float* scores, int accumulate, const void* q, int64_t n_q_rows,
                                const void* k, int64_t n_kv_rows, int64_t k_row_stride,
                                const KeyRot& rot, bool bf16, const int32_t* cu_q,
@@ -122,6 +127,11 @@ struct QueryRot {
   int64_t n_table;
 };
 size_t attn_workspace(const AttnShape& s, bool bf16);
+hipError_t launch_attn_f32(float* out, float* lse, const float* q, const int32_t* row_pos,
+                           int64_t n_rows, const int32_t* cu_rows, const float* k_cache,
+                           const float* v_cache, int64_t n_kv_rows, int64_t kv_row_stride,
+                           const int32_t* cu_kv, const int32_t* kv_pos, const AttnShape& s,
+                           float scale, hipStream_t stream);
 hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_t* row_pos,
                               int64_t n_rows, const int32_t* cu_rows, const void* k_cache,
                               const void* v_cache, int64_t n_kv_rows, int64_t kv_row_stride,

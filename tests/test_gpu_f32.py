@@ -1,0 +1,116 @@
+"""float32 attention and scores at the edges of their tiles (16 query vectors, 16 keys, 8 waves
+taking the key tiles in turn), against the CPU oracle."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import qcfuse as Q
+from paper_2606_05875_amd import qcf
+from parity import assert_close, assert_scores
+from test_gpu_kernels import dev, draw, host, padded, say
+
+pytestmark = pytest.mark.gpu
+
+
+def _batch(n_kv, n_rows):
+    cu = lambda x: np.concatenate([[0], np.cumsum(x)]).astype(np.int32)
+    return cu(n_kv), cu(n_rows)
+
+
+# head groups 1, 2, 4 and 32 (two tiles per row); fewer, exactly and one more than a tile of
+# keys and of query vectors; one to many tiles per wave; a request without rows; padded rows
+@pytest.mark.parametrize("kpos", [False, True])
+@pytest.mark.parametrize("hq,hkv,d,n_kv,n_rows,pad", [
+    (8, 2, 64, [1, 15, 16, 17, 130], [1, 3, 4, 5, 33], 0),
+    (4, 4, 128, [127, 128, 129], [16, 15, 17], 64),
+    (32, 1, 64, [300, 40], [2, 0], 4),
+    (6, 3, 128, [1500], [260], 0),
+])
+def test_attention_f32_edges(hq, hkv, d, n_kv, n_rows, pad, kpos):
+    say("attention f32", hq, hkv, d, n_kv, n_rows, pad, kpos)
+    rng = np.random.default_rng(31)
+    cu_kv, cu_r = _batch(n_kv, n_rows)
+    k = draw(rng, (cu_kv[-1], hkv, d), "f32", 1 / math.sqrt(d))
+    v = draw(rng, (cu_kv[-1], hkv, d), "f32", 1 / math.sqrt(d))
+    q = draw(rng, (cu_r[-1], hq, d), "f32", math.sqrt(d))
+    pos = np.concatenate([np.sort(rng.integers(0, n, m)) for n, m in zip(n_kv, n_rows)]).astype(np.int32)
+    kp = None                                        # explicit positions: ascending, with gaps
+    if kpos:
+        kp = np.concatenate([np.sort(rng.choice(2 * n, n, replace=False)) for n in n_kv]).astype(np.int32)
+        pos *= 2
+    out = torch.full((cu_r[-1], hq, d), float("nan"), device="cuda")
+    lse = torch.empty((cu_r[-1], hq), device="cuda")
+    scale = 1 / math.sqrt(d)
+    qcf.qcf_sparse_prefill_attn(out, dev(q), dev(pos), dev(cu_r), padded(k, pad, torch.float32),
+                                padded(v, pad, torch.float32), dev(cu_kv), max(n_rows), max(n_kv), scale,
+                                kv_pos=dev(kp) if kpos else None, lse=lse)
+    for b in range(len(n_kv)):
+        a, e, ka, ke = cu_r[b], cu_r[b + 1], cu_kv[b], cu_kv[b + 1]
+        if e == a:
+            continue
+        kpb = kp[ka:ke] if kpos else np.arange(ke - ka)
+        want = Q.attention(q[a:e], pos[a:e], k[ka:ke], v[ka:ke], kpb, scale, hkv)
+        assert_close(host(out)[a:e], want, "f32", f"request {b}")
+        vis = kpb <= pos[e - 1]
+        if not vis.any():
+            continue
+        lg = (k[ka:ke][vis, hkv - 1].astype(np.float64) @ q[e - 1, hq - 1].astype(np.float64)) * scale
+        assert abs(float(lse[e - 1, hq - 1]) - np.log(np.exp(lg - lg.max()).sum()) - lg.max()) < 1e-4
+
+
+def test_attention_f32_masked_values_stay_out():
+    """Values of keys that a row does not see never reach it, finite or not (rows of a cache past
+    a request position may hold anything), and a row that sees no key is zero."""
+    say("attention f32, masked rows that are not finite")
+    rng = np.random.default_rng(32)
+    hq, hkv, d, n = 8, 2, 64, 90
+    k, v = (draw(rng, (n, hkv, d), "f32", 1 / math.sqrt(d)) for _ in range(2))
+    q = draw(rng, (5, hq, d), "f32", math.sqrt(d))
+    pos = np.array([20, 20, 21, 21, 21], np.int32)
+    kp = np.arange(n, dtype=np.int32) + 3           # explicit positions: three fewer keys
+    bad_v, bad_k = v.copy(), k.copy()
+    bad_v[22:, :, ::3], bad_k[22:] = np.nan, np.inf
+    cu = dev(np.array([0, 5], np.int32)), dev(np.array([0, n], np.int32))
+    for kv_pos in (None, dev(kp)):
+        got = []
+        for kk, vv in ((k, v), (bad_k, bad_v)):
+            out = torch.empty((5, hq, d), device="cuda")
+            qcf.qcf_sparse_prefill_attn(out, dev(q), dev(pos), cu[0], dev(kk), dev(vv), cu[1], 5, n,
+                                        1 / math.sqrt(d), kv_pos=kv_pos)
+            got.append(host(out))
+        assert np.isfinite(got[1]).all()
+        np.testing.assert_allclose(got[1], got[0], rtol=0, atol=1e-5)
+    bad_v[21, 0, 0] = np.inf                        # seen by rows 2-4 only
+    out = torch.empty((5, hq, d), device="cuda")
+    qcf.qcf_sparse_prefill_attn(out, dev(q), dev(pos), cu[0], dev(k), dev(bad_v), cu[1], 5, n, 1 / math.sqrt(d))
+    inf = ~np.isfinite(host(out))
+    assert not inf[:2].any() and inf[2:, :hq // hkv, 0].all() and inf.sum() == 3 * hq // hkv
+    none = torch.full((5, hq, d), 7.0, device="cuda")
+    qcf.qcf_sparse_prefill_attn(none, dev(q), dev(np.full(5, -1, np.int32)), cu[0], dev(k), dev(v), cu[1], 5, n,
+                                1 / math.sqrt(d))
+    assert not host(none).any()
+
+
+@pytest.mark.parametrize("hq,hkv,d,ctxs,nqs,pad", [
+    (8, 2, 64, [1, 15, 17, 129], [1, 4, 5, 33], 0),
+    (4, 4, 128, [128, 127], [16, 17], 64),
+    (32, 1, 64, [300], [1], 4),
+    (16, 4, 128, [2100], [40], 0),
+])
+def test_scores_f32_edges(hq, hkv, d, ctxs, nqs, pad):
+    say("scores f32", hq, hkv, d, ctxs, nqs, pad)
+    rng = np.random.default_rng(33)
+    cu_kv, cu_q = _batch([c + n for c, n in zip(ctxs, nqs)], nqs)
+    k = draw(rng, (cu_kv[-1], hkv, d), "f32", 1 / math.sqrt(d))
+    q = draw(rng, (cu_q[-1], hq, d), "f32", 1.5 * math.sqrt(d))
+    sc = torch.full((int(cu_kv[-1]),), -5.0, device="cuda")
+    qcf.qcf_probe_scores(sc, dev(q), padded(k, pad, torch.float32), dev(cu_q), dev(cu_kv),
+                         dev(np.array(ctxs, np.int32)), max(nqs), max(ctxs), 1 / math.sqrt(d))
+    got = sc.double().cpu().numpy()
+    for b in range(len(ctxs)):
+        a, n = int(cu_kv[b]), ctxs[b]
+        want = Q.critical_scores(q[cu_q[b]:cu_q[b + 1]], k[a:a + n], 1 / math.sqrt(d), hkv)
+        assert_scores(got[a:a + n], want, f"request {b}")
+        assert np.all(got[a + n:cu_kv[b + 1]] == -5.0)
