@@ -23,9 +23,10 @@
 // sequences with their LDS fragment reads issued four products ahead; on the
 // plain grid the two waves of a SIMD run the step a product phase apart, and
 // one long request hands its row tiles out from per-XCD work queues; a
-// persistent "stream" grid when the row tiles are few and unequal), the probe
+// persistent "stream" grid when the row tiles are few and unequal), large probes
 // on attn_pos_kernel (4 waves, K/V
 // by global->LDS loads two and one tiles ahead, key positions from a table).
+// Calls with few query vectors take attention_keysplit.hip.
 // The fp32 path is attention_f32.hip.
 #include <limits.h>
 #include <math.h>
@@ -33,6 +34,7 @@
 
 #include <algorithm>
 
+#include "qcf_attn.h"
 #include "qcf_device.h"
 #include "qcf_launch.h"
 
@@ -412,34 +414,6 @@ constexpr int kSegCost = 4;
 constexpr int kQueues = 8;
 constexpr int kQueueStride = 32;
 constexpr int kHwRegXccId = (31 << 11) | 20;  // s_getreg: XCC_ID, bits [31:0]
-
-// Turns a lane's query fragments by the rotation of its row's position (Section
-// 2.1.3: a recomputed row's fresh query is rotated at its request position).  The
-// lane holds pieces 16 st + 8 hi + e (e < 8) of slots st < D/16; rotate-half pairs
-// (j, j + D/2) sit in slots st and st + D/32 of the same lane.  tr is the row's
-// D/2 (cos, sin) pairs of qcf_rope_table, and the arithmetic is rope_pair's, so
-// the result is bit for bit the scatter's rotated query.
-template <int D>
-__device__ __forceinline__ void rotate_query(bf16x8 (&qr)[D / 16], const float2* __restrict__ tr,
-                                             int hi) {
-  constexpr int H = D / 32;
-#pragma unroll
-  for (int st = 0; st < H; ++st) {
-    const float4* t4 = reinterpret_cast<const float4*>(tr + 16 * st + 8 * hi);
-    float4 c4[4];
-#pragma unroll
-    for (int i = 0; i < 4; ++i) c4[i] = t4[i];
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      const float4 c = c4[e >> 1];
-      const float2 cs = (e & 1) ? make_float2(c.z, c.w) : make_float2(c.x, c.y);
-      float y1, y2;
-      rope_pair((float)qr[st][e], (float)qr[st + H][e], cs, y1, y2);
-      qr[st][e] = (__bf16)y1;
-      qr[st + H][e] = (__bf16)y2;
-    }
-  }
-}
 
 template <int D, bool kStream, bool kRot>
 __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
@@ -1271,6 +1245,11 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
   const float scale2 = scale * kLog2e;
   int lg = 0;
   while ((1 << lg) < s.hq / s.hkv) ++lg;
+  // the workspace holds stream_layout's bytes whenever attn_workspace asks for one
+  if (bf16 && use_keysplit(s, n_rows, n_kv_rows, kv_pos != nullptr))
+    return launch_attn_keysplit(out, lse, q, row_pos, n_rows, cu_rows, k_cache, v_cache, n_kv_rows,
+                                kv_row_stride, cu_kv, kv_pos, s, scale, ws,
+                                ws ? attn_workspace(s, true) : 0, stream, qrot);
   if (bf16 && !kv_pos) {
     // recomputed rows: the 8-wave kernel (buffer offsets of one request's rows are 32-bit)
     if ((double)s.max_kv * (double)kv_row_stride * 2.0 >= 2147483648.0) return hipErrorInvalidConfiguration;
