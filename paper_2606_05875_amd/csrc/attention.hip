@@ -42,9 +42,6 @@ namespace qcf {
 namespace {
 
 constexpr int kThreads = 256;
-constexpr int kKT = 64;  // keys per tile
-
-__device__ __forceinline__ bf16x8 as_bf16x8(const uint4& v) { return __builtin_bit_cast(bf16x8, v); }
 
 template <int D>
 __global__ __launch_bounds__(kThreads, 2) void attn_pos_kernel(
@@ -353,39 +350,6 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pos_kernel(
 constexpr int kW8 = 8;                // waves per block
 constexpr int kW8Qv = 32 * kW8;       // query vectors per block
 constexpr int kStages = 4;            // LDS ring depth
-constexpr uint32_t kOob = 0x80000000u;  // a buffer offset past every descriptor's range
-
-typedef int i32x4 __attribute__((ext_vector_type(4)));
-
-// Raw buffer descriptor (stride 0): base address, byte range, gfx9 data format word.
-__device__ __forceinline__ i32x4 make_rsrc(const void* base, uint32_t bytes) {
-  const uint64_t a = reinterpret_cast<uint64_t>(base);
-  return i32x4{(int)(uint32_t)a, (int)(uint32_t)(a >> 32) & 0xffff, (int)bytes, 0x00020000};
-}
-
-// LDS byte address of a __shared__ object (32 bits, as the LDS instructions take it)
-__device__ __forceinline__ uint32_t lds_addr(const void* p) {
-  return (uint32_t)reinterpret_cast<uintptr_t>((const __attribute__((address_space(3))) void*)p);
-}
-
-// 16 bytes per lane from the buffer at byte offset voff into LDS at byte
-// address lds + 16 * lane (zeros when voff is past the descriptor's range).
-// Issued as inline assembly so that the compiler adds no waits of its own for
-// it: the caller orders the LDS traffic with explicit counter waits and barriers.
-__device__ __forceinline__ void dma16(const i32x4& rsrc, uint32_t voff, uint32_t lds) {
-  // the LDS address is wave-uniform; readfirstlane keeps it in a scalar register
-  const uint32_t la = __builtin_amdgcn_readfirstlane(lds);
-  asm volatile("s_mov_b32 m0, %0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds"
-               :
-               : "s"(la), "v"(voff), "s"(rsrc)
-               : "memory");
-}
-
-// s_waitcnt with vmcnt <= n and lgkmcnt == 0 (expcnt unconstrained); gfx9 encoding
-template <int N>
-__device__ __forceinline__ void wait_vm_lgkm0() {
-  __builtin_amdgcn_s_waitcnt((N & 15) | ((N >> 4) << 14) | (7 << 4));
-}
 
 // Work of an 8-wave block.  Plain mode: block -> (KV head g, request b, row
 // tile), the tile's whole key range (fixed by the block id, or claimed from a
@@ -814,83 +778,61 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
   };
 
   if (!kStream) {
-    // plain: this block's row tile, all of its keys (up to its largest row
-    // position).  The blocks of one KV head run the requests one after another,
-    // longest (most keys) first, each request's tiles last row tile first:
-    // the blocks that share an XCD then stream the same request's keys through
-    // its L2, and the shortest work comes last.
-    int tile, b = 0;
-    if (queue) {
-      // One request with many row tiles: the items (row tile, KV head) in the order
-      // above are handed out by counters in the workspace.  Queue j holds the tiles
-      // of KV heads j, j + nq, ...; a block takes from the queue of its XCD (whose L2
-      // then serves one head's keys to all of its CUs) and, once that one is empty,
-      // from another that still has items.  Under load the XCDs run at different
-      // clocks, so the fast ones take over tiles that a fixed share per XCD would
-      // leave to the slow ones at the end.  The grid holds spare blocks for that; a
-      // block that finds every queue empty ends at once.
-      const int nq = hkv < kQueues ? hkv : kQueues;
-      const int home = (int)((__builtin_amdgcn_s_getreg(kHwRegXccId) & 15u) % (uint32_t)nq);
-      uint32_t first_claim = 0;  // goes out before the request's row count is read
-      if (threadIdx.x == 0) first_claim = atomicAdd(queue + kQueueStride * home, 1u);
-      const int ntl = min(max_tiles, (max(cu_rows[1] - cu_rows[0], 0) + rpb - 1) / rpb);
-      auto items_of = [&](int j) { return ntl * ((hkv - j + nq - 1) / nq); };
-      // q_next is written only after a barrier that follows every wave's last read of
-      // it; everything derived from it is wave-uniform (scalar registers)
-      auto claim = [&](int j) {
-        __syncthreads();
-        if (threadIdx.x == 0) q_next = (int)atomicAdd(queue + kQueueStride * j, 1u);
-        __syncthreads();
-        return __builtin_amdgcn_readfirstlane(q_next);
-      };
-      auto next_queue = [&](int from) {  // the first queue after `from` with items left, or -1
-        __syncthreads();
-        if (w == 0) {
-          const int c = l < nq ? (int)__hip_atomic_load(queue + kQueueStride * l, __ATOMIC_RELAXED,
-                                                         __HIP_MEMORY_SCOPE_AGENT)
-                               : 0;
-          const bool left = l < nq && c < items_of(l);
-          const int dist = wave_min_i(left ? (l - from - 1 + 2 * nq) % nq : INT_MAX);
-          if (l == 0) q_next = dist == INT_MAX ? -1 : (from + 1 + dist) % nq;
-        }
-        __syncthreads();
-        return __builtin_amdgcn_readfirstlane(q_next);
-      };
-      int qj = home;
-      if (threadIdx.x == 0) q_next = (int)first_claim;
+    // One long request: the items (row tile, KV head), last row tile (most keys) first, are
+    // handed out by counters in the workspace; the tile's whole key range (up to its
+    // largest row position) is this block's.  Queue j holds the tiles of KV heads j,
+    // j + nq, ...; a block takes from the queue of its XCD (whose L2 then serves one
+    // head's keys to all of its CUs) and, once that one is empty, from another that
+    // still has items.  Under load the XCDs run at different clocks, so the fast ones
+    // take over tiles that a fixed share per XCD would leave to the slow ones at the
+    // end.  The grid holds spare blocks for that; a block that finds every queue empty
+    // ends at once.
+    int tile;
+    const int nq = hkv < kQueues ? hkv : kQueues;
+    const int home = (int)((__builtin_amdgcn_s_getreg(kHwRegXccId) & 15u) % (uint32_t)nq);
+    uint32_t first_claim = 0;  // goes out before the request's row count is read
+    if (threadIdx.x == 0) first_claim = atomicAdd(queue + kQueueStride * home, 1u);
+    const int ntl = min(max_tiles, (max(cu_rows[1] - cu_rows[0], 0) + rpb - 1) / rpb);
+    auto items_of = [&](int j) { return ntl * ((hkv - j + nq - 1) / nq); };
+    // q_next is written only after a barrier that follows every wave's last read of
+    // it; everything derived from it is wave-uniform (scalar registers)
+    auto claim = [&](int j) {
       __syncthreads();
-      int item = __builtin_amdgcn_readfirstlane(q_next);
-      while (item >= items_of(qj)) {  // (each failed claim finds a queue empty for good)
-        qj = next_queue(home);
-        if (qj < 0) return;
-        item = claim(qj);
+      if (threadIdx.x == 0) q_next = (int)atomicAdd(queue + kQueueStride * j, 1u);
+      __syncthreads();
+      return __builtin_amdgcn_readfirstlane(q_next);
+    };
+    auto next_queue = [&](int from) {  // the first queue after `from` with items left, or -1
+      __syncthreads();
+      if (w == 0) {
+        const int c = l < nq ? (int)__hip_atomic_load(queue + kQueueStride * l, __ATOMIC_RELAXED,
+                                                       __HIP_MEMORY_SCOPE_AGENT)
+                             : 0;
+        const bool left = l < nq && c < items_of(l);
+        const int dist = wave_min_i(left ? (l - from - 1 + 2 * nq) % nq : INT_MAX);
+        if (l == 0) q_next = dist == INT_MAX ? -1 : (from + 1 + dist) % nq;
       }
-      const int hj = items_of(qj) / ntl;  // KV heads of queue qj
-      const int u = item / hj;
-      tile = ntl - 1 - u;
-      g = qj + nq * (item - u * hj);
-    } else {
-      const int rest = blockIdx.x / hkv;
-      const int rank = rest / max_tiles;
-      tile = max_tiles - 1 - (rest - rank * max_tiles);
-      b = rank;
-      if (batch > 1 && batch <= 64) {
-        // rank of lane j's request: requests with more keys, or as many and a lower index
-        const int nk = l < batch ? cu_kv[l + 1] - cu_kv[l] : -1;
-        int rk = 0;
-        for (int x = 0; x < batch; ++x) {
-          const int nx = __shfl(nk, x, 64);
-          rk += (nx > nk || (nx == nk && x < l)) ? 1 : 0;
-        }
-        const uint64_t hit = __ballot(l < batch && rk == rank);
-        b = __builtin_amdgcn_readfirstlane(hit ? (int)__builtin_ctzll(hit) : rank);
-      }
+      __syncthreads();
+      return __builtin_amdgcn_readfirstlane(q_next);
+    };
+    int qj = home;
+    if (threadIdx.x == 0) q_next = (int)first_claim;
+    __syncthreads();
+    int item = __builtin_amdgcn_readfirstlane(q_next);
+    while (item >= items_of(qj)) {  // (each failed claim finds a queue empty for good)
+      qj = next_queue(home);
+      if (qj < 0) return;
+      item = claim(qj);
     }
-    const int64_t r0 = cu_rows[b];
-    const int nr = cu_rows[b + 1] - (int)r0;
+    const int hj = items_of(qj) / ntl;  // KV heads of queue qj
+    const int u = item / hj;
+    tile = ntl - 1 - u;
+    g = qj + nq * (item - u * hj);
+    const int64_t r0 = cu_rows[0];
+    const int nr = cu_rows[1] - (int)r0;
     if (tile * rpb >= nr) return;
-    const int64_t kv0 = cu_kv[b];
-    int nkv = cu_kv[b + 1] - (int)kv0;
+    const int64_t kv0 = cu_kv[0];
+    int nkv = cu_kv[1] - (int)kv0;
     if (kv0 + nkv > n_kv_rows) nkv = (int)(n_kv_rows - kv0);
     const int rl = tile * rpb + (qv >> lg);
     const int pos_raw = row_pos[min(r0 + rl, n_rows - 1)];
@@ -1180,16 +1122,11 @@ __global__ __launch_bounds__(kThreads) void attn_stream_merge_kernel(
   }
 }
 
-// Stream mode is used when the plain grid would hold fewer than 1.5 blocks per
-// CU and the row tiles fit the block's plan.  (A c3-shaped layer, 392 plain
-// blocks: plain 284 vs stream 297 us; c2, 200 blocks: plain 132 vs stream
-// 103 us.)  Its workspace: the plan (step prefix sums and key ends of up to
-// kMaxStreamTiles row tiles) and two partial slots per block.
-
+// Stream mode is used where 4-wave blocks, one per row tile, would be too few (use_w4) and the
+// row tiles fit the block's plan.  Its workspace: the plan (step prefix sums and key ends of
+// up to kMaxStreamTiles row tiles) and two partial slots per block.
 bool use_stream(const AttnShape& s, int max_tiles) {
-  const int64_t plain_blocks = (int64_t)max_tiles * s.batch * s.hkv;
-  return 2 * plain_blocks < 3 * kStreamBlocks && (int64_t)max_tiles * s.batch <= kMaxStreamTiles &&
-         s.max_kv > kKT;
+  return !use_w4(s) && (int64_t)max_tiles * s.batch <= kMaxStreamTiles && s.max_kv > kKT;
 }
 
 struct StreamLayout {
@@ -1236,23 +1173,26 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
                               int64_t n_rows, const int32_t* cu_rows, const void* k_cache,
                               const void* v_cache, int64_t n_kv_rows, int64_t kv_row_stride,
                               const int32_t* cu_kv, const int32_t* kv_pos, bool bf16,
-                              const AttnShape& s, float scale, void* ws, hipStream_t stream,
+                              const AttnShape& shape, float scale, void* ws, hipStream_t stream,
                               const QueryRot& qrot) {
-  if (n_rows == 0 || s.batch == 0 || s.max_rows == 0) return hipSuccess;
+  if (n_rows == 0 || shape.batch == 0 || shape.max_rows == 0) return hipSuccess;
+  AttnShape s = shape;
+  s.max_rows = (int)std::min<int64_t>(s.max_rows, n_rows);  // no request has more rows than there are
   const bool rot = qrot.table != nullptr;
   if (rot && (!bf16 || kv_pos)) return hipErrorInvalidValue;
   const float2* rtab = reinterpret_cast<const float2*>(qrot.table);
   const float scale2 = scale * kLog2e;
   int lg = 0;
   while ((1 << lg) < s.hq / s.hkv) ++lg;
+  // recomputed rows: the buffer offsets of one request's rows are 32-bit
+  if (bf16 && !kv_pos && (double)s.max_kv * (double)kv_row_stride * 2.0 >= 2147483648.0)
+    return hipErrorInvalidConfiguration;
   // the workspace holds stream_layout's bytes whenever attn_workspace asks for one
   if (bf16 && use_keysplit(s, n_rows, n_kv_rows, kv_pos != nullptr))
     return launch_attn_keysplit(out, lse, q, row_pos, n_rows, cu_rows, k_cache, v_cache, n_kv_rows,
                                 kv_row_stride, cu_kv, kv_pos, s, scale, ws,
                                 ws ? attn_workspace(s, true) : 0, stream, qrot);
   if (bf16 && !kv_pos) {
-    // recomputed rows: the 8-wave kernel (buffer offsets of one request's rows are 32-bit)
-    if ((double)s.max_kv * (double)kv_row_stride * 2.0 >= 2147483648.0) return hipErrorInvalidConfiguration;
     const int max_tiles = (s.max_rows + (kW8Qv >> lg) - 1) / (kW8Qv >> lg);
     if (use_stream(s, max_tiles)) {
       const StreamLayout L = stream_layout(s);
@@ -1279,22 +1219,21 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
 #undef QCF_W8S
       return hipGetLastError();
     }
-    const int64_t nblocks = (int64_t)max_tiles * s.batch * s.hkv;
-    if (nblocks > 0x7fffffff) return hipErrorInvalidConfiguration;
-    dim3 grid((unsigned)nblocks);
-    // One request with at least four row tiles per CU: the tiles come from work queues
-    // (counters in the workspace, reset by a kernel on the same stream), and an eighth
-    // more blocks let the fast XCDs take tiles from the slow ones.  Measured on one box:
-    // 32 x 1024-token context (9.7 tiles per CU) -1.7 to -2.1%, 16 x 1024 (4.9) -1%,
-    // 8 x 1024 (2.4) +1.9%, ragged 16-request batch +1 to +2%, so fewer tiles or
-    // several requests keep the fixed order.
-    uint32_t* queue = nullptr;
-    if (ws && s.batch == 1 && nblocks >= 4 * (int64_t)cu_count() &&
-        nblocks + nblocks / 8 <= 0x7fffffff) {
-      queue = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + stream_layout(s).queue_off);
-      attn_queue_reset_kernel<<<1, 64, 0, stream>>>(queue);
-      grid = dim3((unsigned)(nblocks + nblocks / 8));
-    }
+    // One request with at least four row tiles per CU: 8-wave blocks whose tiles come from work
+    // queues (counters in the workspace, reset by a kernel on the same stream); an eighth
+    // more blocks let the fast XCDs take tiles from the slow ones.  Measured on one box
+    // against the fixed order: 32 x 1024-token context (9.7 tiles per CU) -1.7 to -2.1%,
+    // 16 x 1024 (4.9) -1%, 8 x 1024 (2.4) +1.9%, ragged 16-request batch +1 to +2%.  Other
+    // calls take the 4-wave blocks in a fixed order.
+    const int64_t nblocks = (int64_t)max_tiles * s.hkv;
+    if (!ws || s.batch != 1 || nblocks < 4 * (int64_t)cu_count() ||
+        nblocks + nblocks / 8 > 0x7fffffff)
+      return launch_attn_w4(out, lse, q, row_pos, n_rows, cu_rows, k_cache, v_cache, n_kv_rows,
+                            kv_row_stride, cu_kv, s, scale, stream, qrot);
+    const dim3 grid((unsigned)(nblocks + nblocks / 8));
+    uint32_t* queue =
+        reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + stream_layout(s).queue_off);
+    attn_queue_reset_kernel<<<1, 64, 0, stream>>>(queue);
 #define QCF_W8(D, R)                                                                              \
   attn_w8_kernel<D, false, R><<<grid, kW8 * 64, 0, stream>>>(                                     \
       static_cast<uint16_t*>(out), lse, static_cast<const uint16_t*>(q), row_pos, n_rows, cu_rows, \

@@ -1,0 +1,60 @@
+"""Recomputed-row attention on 4-wave blocks (128 query vectors, 64-key tiles in an XOR-permuted LDS
+layout) where it can go wrong: tile remainders, key tails, head groups, more requests than the
+block order ranks, no workspace, rotated queries read through an index; against the CPU oracle."""
+import math
+
+import numpy as np
+import pytest
+import torch
+
+from oracle import qcfuse as Q
+from paper_2606_05875_amd import qcf
+from parity import assert_close
+from test_gpu_kernels import dev, draw, host, padded, say
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_kv,n_rows,pad,rot", [
+    (32, 8, 128, [200] * 70, [180] * 70, 0, False),               # 70 requests: no ranking by length
+    (32, 8, 128, [64, 63, 65, 1] * 12, [64, 33, 31, 1] * 12, 128, True),
+    (16, 2, 64, [1500, 40, 1300], [1400, 31, 777], 64, False),     # group 8, head size 64
+    (8, 8, 64, [700, 129], [650, 129], 0, True),                   # group 1
+    (32, 1, 128, [900, 512], [900, 300], 0, True),                 # group 32: 4 rows per block
+    (64, 8, 128, [64] * 40, [64] * 40, 0, False),                  # 64 keys: no workspace
+    (40, 10, 128, [2000], [1700], 128, True),
+])
+def test_attention_w4(hq, hkv, d, n_kv, n_rows, pad, rot):
+    say("attention, 4-wave blocks", hq, hkv, d, len(n_kv), max(n_kv), pad, rot)
+    rng = np.random.default_rng(51)
+    cu = lambda x: np.concatenate([[0], np.cumsum(x)]).astype(np.int32)
+    cu_kv, cu_r = cu(n_kv), cu(n_rows)
+    k = draw(rng, (cu_kv[-1], hkv, d), "bf16", 1 / math.sqrt(d))
+    v = draw(rng, (cu_kv[-1], hkv, d), "bf16", 1 / math.sqrt(d))
+    pos = np.concatenate([np.sort(rng.choice(n, m, replace=False)) for n, m in zip(n_kv, n_rows)]).astype(np.int32)
+    n, src = int(cu_r[-1]), None
+    q = draw(rng, (n + 3, hq, d), "bf16", math.sqrt(d))
+    out = torch.full((n, hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    lse = torch.empty((n, hq), device="cuda")
+    geo = (dev(pos), dev(cu_r), padded(k, pad, torch.bfloat16), padded(v, pad, torch.bfloat16), dev(cu_kv),
+           max(n_rows), max(n_kv), 1 / math.sqrt(d))
+    if rot:
+        src = rng.permutation(n + 3)[:n].astype(np.int32)
+        qcf.qcf_sparse_prefill_attn_rope(out, dev(q, torch.bfloat16), *geo,
+                                         qcf.rope_position_table(max(n_kv), d, 1e6), q_src=dev(src), lse=lse)
+        q = Q.round_storage(Q.rope(q[src], pos, 1e6), "bf16")
+    else:
+        q = q[:n]
+        qcf.qcf_sparse_prefill_attn(out, dev(q, torch.bfloat16), *geo, lse=lse)
+    got, rpb = host(out), 128 // (hq // hkv)
+    assert np.isfinite(got).all()
+    for b in range(0, len(n_kv), 1 if len(n_kv) < 8 else 9):
+        a, e, ka, ke = cu_r[b], cu_r[b + 1], cu_kv[b], cu_kv[b + 1]
+        first = np.arange(a, e, rpb)                # the first and last row of every row tile
+        pick = np.unique(np.concatenate([first, np.minimum(first + rpb - 1, e - 1)]))
+        want = Q.round_storage(Q.attention(q[pick], pos[pick], k[ka:ke], v[ka:ke], np.arange(ke - ka),
+                                           1 / math.sqrt(d), hkv), "bf16")
+        assert_close(got[pick], want, "bf16", f"request {b}")
+        r, h = pick[-1], hq - 1
+        lg = (k[ka:ka + pos[r] + 1, hkv - 1].astype(np.float64) @ q[r, h].astype(np.float64)) / math.sqrt(d)
+        assert abs(float(lse[r, h]) - np.log(np.exp(lg - lg.max()).sum()) - lg.max()) < 2e-3
