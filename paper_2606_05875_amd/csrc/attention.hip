@@ -18,14 +18,13 @@
 //  * online softmax in float32 (base-2 exponentials) with a lazy rescale;
 //    the causal limit masks only tiles that reach past the wave's smallest
 //    position, and waves skip tiles past their largest position.
-// Recomputed rows run on attn_w8_kernel (8 waves, 256 query vectors, a
-// 4-stage K/V ring filled by buffer loads; the products run as fenced
-// sequences with their LDS fragment reads issued four products ahead; on the
-// plain grid the two waves of a SIMD run the step a product phase apart, and
-// one long request hands its row tiles out from per-XCD work queues; a
-// persistent "stream" grid when the row tiles are few and unequal), large probes
-// on attn_pos_kernel (4 waves, K/V
-// by global->LDS loads two and one tiles ahead, key positions from a table).
+// Recomputed rows: one long request on attn_w8_kernel (8 waves, 256 query vectors, a
+// 4-stage K/V ring filled by buffer loads; the products run as fenced sequences with
+// their LDS fragment reads issued four products ahead; the two waves of a SIMD run the
+// step a product phase apart, and the row tiles come from per-XCD work queues); few,
+// unequal row tiles on its persistent "stream" grid; all others on 4-wave blocks
+// (attention_w4.hip).  Large probes run on attn_pos_kernel (4 waves, K/V by global->LDS
+// loads two and one tiles ahead, key positions from a table).
 // Calls with few query vectors take attention_keysplit.hip.
 // The fp32 path is attention_f32.hip.
 #include <limits.h>
@@ -338,12 +337,15 @@ __global__ __launch_bounds__(kThreads, 2) void attn_pos_kernel(
 // per wave, with the same per-wave tile step as attn_pos_kernel.  One block
 // fills a CU (two waves per SIMD), which leaves LDS for a 4-stage ring of
 // K/V tiles: step t fetches K(t+3), first read in step t+2, and V(t+3) (V(t+2)
-// on the split plain grid), first read in step t+3 (t+2), and a step ends by
+// on the split schedule of the queues), first read in step t+3 (t+2), and a step ends by
 // waiting only for the tiles fetched one step earlier, so every global->LDS
 // transfer has at least two steps to land.  The transfers are buffer loads
 // with an LDS destination: a per-(request, head) descriptor bounds the key
-// range, so rows past the last key and the LDS padding chunks read as zeros
-// without touching memory, and a tile only moves a scalar row offset.  (Tiles
+// range, so rows past the last key read as zeros without touching memory, and a
+// tile only moves a scalar row offset.  LDS rows are unpadded with their chunks
+// XORed by the row (attention_w4.hip): 32 transfers per step where padded rows
+// took 37 (bit-identical; persistent grid: 5 x 512-token layer 57.2 -> 55.6 us, at
+// head size 64 77.6 -> 74.1; one 32K request unchanged at 4.55 ms).  (Tiles
 // staged through registers -- 16-byte loads one step ahead, then plain LDS
 // writes -- measured 3% slower on the c2 call with its inputs cold in the
 // caches: one step of latency cover instead of two.)
@@ -389,22 +391,20 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
     uint16_t* __restrict__ part_o, float2* __restrict__ part_ml,
     const int32_t* __restrict__ q_src, int64_t n_q_src, const float2* __restrict__ rtab,
     int n_tab, uint32_t* __restrict__ queue) {
-  constexpr int KCH = D / 8 + 1, VCH = D / 8 + 4;  // 16-byte chunks per LDS row (padded)
-  constexpr int KSTR = KCH * 8, VSTR = VCH * 8;    // bf16 elements per LDS row
-  constexpr int KST = kKT * KSTR, VST = kKT * VSTR;  // elements per stage
-  constexpr int NSLOT = KCH + VCH;                   // 64-lane transfers per stage
-  constexpr int SPW = (NSLOT + kW8 - 1) / kW8;       // transfers per wave (the first waves)
-  constexpr int NFULL = NSLOT - (SPW - 1) * kW8;     // waves that issue SPW of them
+  constexpr int CH = D / 8;            // 16-byte chunks per LDS row
+  constexpr int RPS = 64 / CH;         // rows per 64-lane transfer
+  constexpr int RB = D * 2;            // bytes per LDS row
+  constexpr int ST = kKT * RB;         // bytes per stage
+  constexpr int SLOTS = kKT / RPS;     // transfers per stage, K or V
   // Plain mode splits the block: waves 0-3 (one per SIMD) load the K chunks of a stage and
   // multiply P(t) V(t) in step t; waves 4-7 load the V chunks and multiply P(t) V(t) at the
   // start of step t+1.  The stream grid keeps one schedule for all waves.
   constexpr bool kDefer = !kStream;
-  constexpr int SPWK = (KCH + 3) / 4, SPWV = (VCH + 3) / 4;  // transfers per wave, split
-  constexpr int SPWX = kDefer ? (SPWK > SPWV ? SPWK : SPWV) : SPW;
-  __shared__ __attribute__((aligned(16))) uint16_t k_lds[kStages * KST];
-  __shared__ __attribute__((aligned(16))) uint16_t v_lds[kStages * VST];
+  constexpr int SPW = 2 * SLOTS / kW8;  // transfers per wave and step (K and V, or, split, one of them)
+  __shared__ __attribute__((aligned(1024))) uint8_t k_lds[kStages * ST];
+  __shared__ __attribute__((aligned(1024))) uint8_t v_lds[kStages * ST];
   __shared__ int red[kW8];
-  __shared__ int q_next;  // plain grid with queues: a claimed item or a queue
+  __shared__ int q_next;  // queues: a claimed item or a queue
   __shared__ int plan_cum[kStream ? kMaxStreamTiles + 1 : 1];
   __shared__ int plan_end[kStream ? kMaxStreamTiles : 1];
   __shared__ int req_rows[kStream ? kMaxStreamTiles + 1 : 1];  // cu_rows, cu_kv of the call
@@ -418,12 +418,13 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
   const int rpb = kW8Qv >> lg;
   const uint32_t k_base = lds_addr(k_lds), v_base = lds_addr(v_lds);
   const int qv = 32 * w + lq;
-  int g = blockIdx.x % hkv;  // (plain grid with queues: set from the claimed item)
+  int g = blockIdx.x % hkv;  // (queues: set from the claimed item)
 
   const uint32_t row_b = (uint32_t)(kv_stride * 2);
   const int tg = l >> 4, te = (l >> 2) & 3, tq = l & 3;
-  const int vrd = (4 * (tg >> 1) + te) * VSTR + 16 * (tg & 1) + 4 * tq;
-  const int krd = lq * KSTR + 8 * hi;
+  const int ky = D == 128 ? lq & 15 : (lq >> 1) & 7;
+  const int krd = lq * RB + (hi ^ (ky & 1)) * 16 + (ky >> 1) * 32;
+  const int vrd = (4 * (tg >> 1) + te) * RB + (D == 128 ? te : te >> 1) * 64 + 32 * (tg & 1) + 8 * tq;
   typedef short v4s __attribute__((ext_vector_type(4)));
   typedef v4s __attribute__((address_space(3))) * lds_v4s;
   typedef float f32x2_t __attribute__((ext_vector_type(2)));
@@ -444,49 +445,34 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
     const uint32_t range = nkv > 0 ? (uint32_t)(nkv - 1) * row_b + D * 2 : 0u;
     const i32x4 rk = make_rsrc(kc + kv0 * kv_stride + (int64_t)g * D, range);
     const i32x4 rv = make_rsrc(vc + kv0 * kv_stride + (int64_t)g * D, range);
-    // this wave's transfer slots: j = w + 8 i over the K then the V chunks of a stage,
-    // or, split, j = (w & 3) + 4 i over the K chunks (waves 0-3) or the V chunks
-    // (waves 4-7).  Slot j fills chunks [64 j, 64 j + 64) of its tile; lane l fills
-    // chunk 64 j + l = (row, column) of the padded tile.
     const bool vwave = kDefer && w >= 4;
-    uint32_t soff[SPWX];
-    bool sk[SPWX];  // slot i fills K chunks
-    int sj[SPWX];   // chunk slot within its tile
-#pragma unroll
-    for (int i = 0; i < SPWX; ++i) {
-      int j;
-      if (kDefer) {
-        j = (w & 3) + 4 * i;
-        sk[i] = !vwave;
-      } else {
-        j = w + kW8 * i;
-        sk[i] = j < KCH;
-        if (!sk[i]) j -= KCH;
-      }
-      const int ch = sk[i] ? KCH : VCH;  // chunks per row of the slot's tile
-      sj[i] = j;
-      const int ci = j * 64 + l;
-      const int r = ci / ch, c = ci % ch;
-      soff[i] = (j < ch && c < D / 8) ? (uint32_t)r * row_b + c * 16 : kOob;
-    }
-    const int nslots = kDefer ? (vwave ? (VCH - (w & 3) + 3) / 4 : (KCH - (w & 3) + 3) / 4)
-                              : (w < NFULL ? SPW : SPW - 1);
+    // transfer i of a wave fills rows dr + i RPS NW of its tile (NW waves share the tile)
+    constexpr int NW = kDefer ? 4 : kW8;
+    const int wi = kDefer ? (w & 3) : w;
+    const int dr = RPS * wi + l / CH, dc = l % CH;
+    const uint32_t koff = (uint32_t)dr * row_b + (dc ^ (D == 128 ? dr & 15 : (dr >> 1) & 7)) * 16;
+    const uint32_t voff = (uint32_t)dr * row_b + (dc ^ (4 * (D == 128 ? dr & 3 : (dr >> 1) & 1))) * 16;
     // the transfers of one step: tile r (relative to the segment's first tile)
     // into stage r % 4, K and V (split: this wave's part, K or V); a tile past the
     // segment's end reads zeros
     const int t0 = kt_lo / kKT;
     const int nt = kt_hi > kt_lo ? (kt_hi - kt_lo + kKT - 1) / kKT : 0;
-    auto issue = [&](int r) {
+    auto issue1 = [&](int r, int i, bool isk) {
       const int sg = r & (kStages - 1);
-      const uint32_t toff = (uint32_t)((t0 + r) * kKT) * row_b;
+      const uint32_t soff = r < nt ? (uint32_t)((t0 + r) * kKT + RPS * NW * i) * row_b : kOob;
+      const uint32_t dst = (uint32_t)(sg * ST + (wi + NW * i) * 1024);
+      if (isk) dma16(rk, koff + soff, k_base + dst);
+      else dma16(rv, voff + soff, v_base + dst);
+    };
+    auto issue = [&](int r) {
+      if (kDefer) {
 #pragma unroll
-      for (int i = 0; i < SPWX; ++i) {
-        if (i >= nslots) break;
-        const uint32_t off = r < nt ? soff[i] + toff : kOob;
-        if (sk[i])
-          dma16(rk, off, k_base + (uint32_t)(sg * KST + sj[i] * 512) * 2u);
-        else
-          dma16(rv, off, v_base + (uint32_t)(sg * VST + sj[i] * 512) * 2u);
+        for (int i = 0; i < SPW; ++i) issue1(r, i, !vwave);
+      } else {
+#pragma unroll
+        for (int i = 0; i < SPW / 2; ++i) issue1(r, i, true);
+#pragma unroll
+        for (int i = 0; i < SPW / 2; ++i) issue1(r, i, false);
       }
     };
     // The first three key tiles go out before anything waits on memory (every
@@ -524,15 +510,14 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
     // (and every LDS read) are complete, then the block meets
     auto step_barrier = [&]() {
       asm volatile("" ::: "memory");
-      if (nslots == SPWX) wait_vm_lgkm0<SPWX>();
-      else wait_vm_lgkm0<SPWX - 1>();
+      wait_vm_lgkm0<SPW>();
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
     };
-    auto qk_half = [&](const uint16_t* kl, int hb, f32x16& sh) {
+    auto qk_half = [&](const uint8_t* kl, int hb, f32x16& sh) {
       bf16x8 kf[D / 16];
 #pragma unroll
-      for (int st = 0; st < D / 16; ++st) kf[st] = as_bf16x8(ld16(kl + hb * 32 * KSTR + 16 * st));
+      for (int st = 0; st < D / 16; ++st) kf[st] = as_bf16x8(ld16(kl + hb * 32 * RB + (krd ^ (st << 5))));
       sh = f32x16{};
 #pragma unroll
       for (int st = 0; st < D / 16; ++st)
@@ -592,13 +577,13 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
     // and the same order of the row sum as qk_half twice + softmax_exp, so bit-identical (c4
     // -1.2%, c5 -1.8%).  Plain mode only: the stream kernel has fewer registers to spare and
     // spilled with it.
-    auto qk_exp_fused = [&](const uint16_t* kl, f32x16 (&sn)[2], f32x16 (&sc)[2], bf16x8 (&pb)[2][2]) {
+    auto qk_exp_fused = [&](const uint8_t* kl, f32x16 (&sn)[2], f32x16 (&sc)[2], bf16x8 (&pb)[2][2]) {
       constexpr int NS = D / 16;    // products per 32-key half
       constexpr int NM = 2 * NS;    // products per tile
       constexpr int EG = 32 / NM;   // elements of the tile per group (2 at D = 128)
       constexpr int PF = 4;         // K fragments in flight
       static_assert(EG % 2 == 0 && EG * NM == 32, "groups cover the tile in element pairs");
-      auto kfrag = [&](int i) { return as_bf16x8(ld16(kl + (i / NS) * 32 * KSTR + 16 * (i % NS))); };
+      auto kfrag = [&](int i) { return as_bf16x8(ld16(kl + (i / NS) * 32 * RB + (krd ^ ((i % NS) << 5)))); };
       bf16x8 kf[NM];
 #pragma unroll
       for (int i = 0; i < PF; ++i) kf[i] = kfrag(i);
@@ -641,15 +626,15 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
     // reads) of the product four places ahead: the compiler's own order read eight fragments
     // at a time and waited at the head of every batch (bit-identical; c4 -0.8%, c5 -1.0%,
     // c2 (stream mode) -4%).
-    auto pv = [&](const uint16_t* vl, bf16x8 (&pb)[2][2]) {
+    auto pv = [&](const uint8_t* vl, bf16x8 (&pb)[2][2]) {
       constexpr int NB = D / 32;
       constexpr int NM = 4 * NB;  // products, ordered (hb, k2, mb)
       constexpr int PF = 4;       // V fragments in flight
       auto vfrag = [&](int j) {
         const int hb = j / (2 * NB), k2 = (j / NB) % 2, mb = j % NB;
-        const uint16_t* p0 = vl + (hb * 32 + 16 * k2) * VSTR + 32 * mb;
+        const uint8_t* p0 = vl + (hb * 32 + 16 * k2) * RB + (vrd ^ (mb << 6));
         const v4s lo = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p0));
-        const v4s up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p0 + 8 * VSTR));
+        const v4s up = __builtin_amdgcn_ds_read_tr16_b64_v4i16((lds_v4s)(p0 + 8 * RB));
         return __builtin_bit_cast(bf16x8, __builtin_shufflevector(lo, up, 0, 1, 2, 3, 4, 5, 6, 7));
       };
       bf16x8 vf[NM];
@@ -687,8 +672,8 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
     if (nt > 0 && kt_lo < wave_end) {
-      qk_half(k_lds + krd, 0, sa[0]);
-      qk_half(k_lds + krd, 1, sa[1]);
+      qk_half(k_lds, 0, sa[0]);
+      qk_half(k_lds, 1, sa[1]);
     }
     bf16x8 pb[2][2];
     bool pend = false;  // split, waves 4-7: pb holds P of the previous tile
@@ -697,7 +682,7 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
       const bool do_cur = kt0 < wave_end;
       const bool do_next = t + 1 < nt && kt0 + kKT < wave_end;
       if (vwave) {
-        if (pend) pv(v_lds + ((t - 1) & 3) * VST + vrd, pb);
+        if (pend) pv(v_lds + ((t - 1) & 3) * ST, pb);
         issue(t + 2);
       }
       if (do_cur) softmax_pre(sc, kt0);
@@ -707,8 +692,8 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
       // products (c4 4887 -> 4804 us, c5 -1.8%, bit-identical).
       __builtin_amdgcn_s_setprio(1);
       if (do_next) {
-        const uint16_t* kn = k_lds + ((t + 1) & 3) * KST + krd;
-        if constexpr (!kStream) {
+        const uint8_t* kn = k_lds + ((t + 1) & 3) * ST;
+        if constexpr (!kStream || D == 64) {  // (at 128 it spills in stream mode)
           qk_exp_fused(kn, sn, sc, pb);
         } else {
           qk_half(kn, 0, sn[0]);
@@ -728,7 +713,7 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
         pend = do_cur;
       } else {
         issue(t + 3);
-        if (do_cur) pv(v_lds + (t & 3) * VST + vrd, pb);
+        if (do_cur) pv(v_lds + (t & 3) * ST, pb);
       }
       step_barrier();
     };
@@ -737,7 +722,7 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
       if (t + 1 < nt) step(t + 1, sb, sa);
     }
     if (kDefer && nt > 0) {
-      if (pend) pv(v_lds + ((nt - 1) & 3) * VST + vrd, pb);
+      if (pend) pv(v_lds + ((nt - 1) & 3) * ST, pb);
       step_barrier();
     }
     // drain the last (zero-row) transfers before the LDS is refilled or released
@@ -956,7 +941,7 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
   }
 }
 
-// Sets the plain grid's work counters to zero before the grid starts (a kernel
+// Sets the work counters to zero before the grid starts (a kernel
 // rather than a memset, so that the call can be captured in a graph).
 __global__ void attn_queue_reset_kernel(uint32_t* __restrict__ queue) {
   if (threadIdx.x < kQueues) queue[kQueueStride * threadIdx.x] = 0u;
