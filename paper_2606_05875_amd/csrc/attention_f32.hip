@@ -108,6 +108,10 @@ __global__ __launch_bounds__(kW * 64) void attn_f32_kernel(
       load_k(kt0);
       load_v(kt0);
     }
+    // Q has to be there before the loop (a wait for it inside would count the next tile's loads)
+#pragma unroll
+    for (int sb = 0; sb < SB; ++sb)
+      asm volatile("" : "+v"(qf[sb].x), "+v"(qf[sb].y), "+v"(qf[sb].z), "+v"(qf[sb].w));
     for (; kt0 < jend; kt0 += kW * kKeys) {
       f32x4 s[4] = {};  // summed pairwise: shorter chains round less
       bool vis[4];  // key visible to this lane's query vector

@@ -116,6 +116,10 @@ __global__ __launch_bounds__(kW * 64) void scores_stats_f32(
     float m = -1e30f, ls = 0.f;
     int kt0 = w * kTile;
     if (kt0 < N) load_k(kf, kt0);
+    // Q has to be there before the loop (a wait for it inside would count the next tile's loads)
+#pragma unroll
+    for (int sb = 0; sb < D / 16; ++sb)
+      asm volatile("" : "+v"(qf.f[sb].x), "+v"(qf.f[sb].y), "+v"(qf.f[sb].z), "+v"(qf.f[sb].w));
     for (; kt0 < N; kt0 += kW * kTile) {
       if (kt0 + kW * kTile < N) load_k(kn, kt0 + kW * kTile);
       const f32x4 s = product<D>(kf, qf);
