@@ -41,6 +41,7 @@ namespace qcf {
 namespace {
 
 constexpr int kThreads = 256;
+constexpr int kKT = 64;  // keys per tile
 
 template <int D>
 __global__ __launch_bounds__(kThreads, 2) void attn_pos_kernel(

@@ -37,6 +37,7 @@ namespace {
 
 constexpr int kW = 4;           // waves per block
 constexpr int kQv = 32 * kW;    // query vectors per block
+constexpr int kKT = 64;         // keys per tile
 
 template <int D, bool kRot>
 __global__ __launch_bounds__(kW * 64, 2) void attn_w4_kernel(

@@ -4,7 +4,6 @@
 
 namespace qcf {
 
-constexpr int kKT = 64;  // keys per tile of the shared-tile kernels
 constexpr uint32_t kOob = 0x80000000u;  // a buffer offset past every descriptor's range
 
 __device__ __forceinline__ bf16x8 as_bf16x8(const uint4& v) { return __builtin_bit_cast(bf16x8, v); }
