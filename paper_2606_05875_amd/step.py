@@ -252,14 +252,22 @@ class FusionStep:
         self.ev_context = torch.cuda.Event()
 
     # -- stages ---------------------------------------------------------------
-    def _call(self, key, fn, *args, **kw):
+    def _replay(self, key):
+        """Launch the stage's prepared call; False on its first use."""
         p = self._prep.get(key)
         if p is None:
-            p = self._prep[key] = qcf.prepare(fn, *args, **kw)
+            return False
         p(self._stream)
+        return True
+
+    def _call(self, key, fn, *args, **kw):
+        self._prep[key] = qcf.prepare(fn, *args, **kw)
+        self._replay(key)
 
     def stage_assemble(self):
         """Request cache (chunks re-positioned, values stitched), query rows, probe buffer."""
+        if self._replay("assemble"):
+            return
         w, p = self.w, self.plan
         self._call("assemble", qcf.qcf_assemble, self.k, self.v, self.k_pic, self.v_pic,
                    self.seg_start, self.seg_len, self.seg_delta, p.max_seg, self.q_new, self.k_new,
@@ -269,6 +277,8 @@ class FusionStep:
 
     def stage_query_assemble(self):
         """Query rows (cache rows, q_u) and the probe buffer; the context is left alone."""
+        if self._replay("query_assemble"):
+            return
         w = self.w
         self._call("query_assemble", qcf.qcf_assemble, self.k, self.v, self.k_pic, self.v_pic,
                    self.no_seg, self.no_seg, self.no_seg, 0, self.q_new, self.k_new, self.v_new,
@@ -276,11 +286,15 @@ class FusionStep:
                    self.probe_delta, w.rope_theta, query_src=self.u_idx, query_slot=self.query_slot)
 
     def stage_rope_table(self):
+        if self._replay("rope_table"):
+            return
         if self.w.n_chunks:
             self._call("rope_table", qcf.qcf_rope_table, self.rope_table, self.seg_delta,
                        self.w.rope_theta)
 
     def stage_scores_pic(self, accumulate=False):
+        if self._replay(("scores_pic", accumulate)):
+            return
         p = self.plan
         self._call(("scores_pic", accumulate), qcf.qcf_probe_scores_pic, self.scores, self.q_u,
                    self.k_pic, self.key_rot, self.rope_table, self.cu_q, self.cu_kv, self.ctx_len,
@@ -288,26 +302,35 @@ class FusionStep:
 
     # the same work as three separate calls (kept for the stage-by-stage tests)
     def stage_rerope(self):
+        if self._replay("rerope"):
+            return
         w, p = self.w, self.plan
         self._call("rerope", qcf.qcf_rerope, self.k, self.k_pic, self.seg_start, self.seg_len,
                    self.seg_delta, p.max_seg, w.rope_theta, v_out=self.v, v_in=self.v_pic)
 
     def stage_query_rows(self):
+        if self._replay("query_rows"):
+            return
         self._call("query_rows", qcf.qcf_scatter_kv, self.k, self.v, self.k_new, self.v_new,
                    self.u_idx, self.u_pos, self.w.rope_theta, q_new=self.q_new, q_out=self.q_u,
                    src_idx=self.u_idx)
 
     def stage_anchor_gather(self):
-        self._call("gather_k", qcf.qcf_gather_rows, self.k_probe, self.k, self.probe_idx)
-        self._call("gather_v", qcf.qcf_gather_rows, self.v_probe, self.v, self.probe_idx)
+        for key, dst, src in (("gather_k", self.k_probe, self.k), ("gather_v", self.v_probe, self.v)):
+            if not self._replay(key):
+                self._call(key, qcf.qcf_gather_rows, dst, src, self.probe_idx)
 
     def stage_probe_attn(self):
+        if self._replay("probe_attn"):
+            return
         p = self.plan
         self._call("probe_attn", qcf.qcf_sparse_prefill_attn, self.o_probe, self.q_u, self.u_pos,
                    self.cu_q, self.k_probe, self.v_probe, self.cu_probe, p.max_q, p.max_probe,
                    self.scale, kv_pos=self.probe_pos, workspace=self.ws_probe)
 
     def stage_scores(self, accumulate=False):
+        if self._replay(("scores", accumulate)):
+            return
         p = self.plan
         self._call(("scores", accumulate), qcf.qcf_probe_scores, self.scores, self.q_u, self.k,
                    self.cu_q, self.cu_kv, self.ctx_len, p.max_q, p.max_ctx, self.scale,
@@ -316,6 +339,8 @@ class FusionStep:
     def stage_scores_select(self, accumulate=False):
         """Scores and the selection in one call (the last score pass and the selection share a
         launch); results identical to stage_scores then stage_select."""
+        if self._replay(("scores_select", accumulate)):
+            return
         p = self.plan
         self._call(("scores_select", accumulate), qcf.qcf_probe_scores_select, self.scores,
                    self.q_u, self.k, self.cu_q, self.cu_kv, self.ctx_len, p.max_q, p.max_ctx,
@@ -324,12 +349,16 @@ class FusionStep:
                    accumulate=accumulate, workspace=self.ws_scores)
 
     def stage_select(self):
+        if self._replay("select"):
+            return
         p = self.plan
         self._call("select", qcf.qcf_select_topk, self.R_idx, self.scores, self.sel_start,
                    self.sel_len, self.seg_k, self.out_start, p.max_sel, out_pos=self.R_pos,
                    pos_base=self.pos_base)
 
     def stage_scatter(self):
+        if self._replay("scatter"):
+            return
         if self.rot_in_attn:
             self._call("scatter", qcf.qcf_scatter_kv, self.k, self.v, self.k_new, self.v_new,
                        self.R_idx, self.R_pos, self.w.rope_theta, src_idx=self.R_idx)
@@ -339,6 +368,8 @@ class FusionStep:
                        src_idx=self.R_idx)
 
     def stage_attn(self):
+        if self._replay("attn"):
+            return
         p = self.plan
         if self.rot_in_attn:
             self._call("attn", qcf.qcf_sparse_prefill_attn_rope, self.o, self.q_new, self.R_pos,
