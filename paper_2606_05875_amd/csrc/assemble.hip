@@ -41,7 +41,7 @@ struct AssembleArgs {
   const int32_t *probe_src, *probe_delta;
   int probe_rows_per_block;
   int hq, hkv;
-  double theta;
+  RopeFreq freq;
 };
 
 template <typename T, int D, bool kStreamIn>
@@ -61,7 +61,7 @@ __global__ __launch_bounds__(kThreads) void assemble_kernel(AssembleArgs<T, D> A
     const int64_t s0 = (A.src_start ? (int64_t)A.src_start[s] : (int64_t)A.seg_start[s]) + r0;
     // the angle table first: forming it while this kernel's loads are in flight
     // holds them across the float64 work and costs occupancy (measured slower)
-    if (threadIdx.x < HALF) cs[threadIdx.x] = rope_cs((double)A.seg_delta[s], threadIdx.x, D, A.theta);
+    if (threadIdx.x < HALF) cs[threadIdx.x] = rope_cs((double)A.seg_delta[s], threadIdx.x, A.freq);
     __syncthreads();
     remap_rows<T, D, kThreads, kUnits, kStreamIn, true>(
         A.k_cache, A.v_cache, A.row_stride, A.k_pic, A.v_pic, A.pic_stride, s0, d0,
@@ -76,7 +76,7 @@ __global__ __launch_bounds__(kThreads) void assemble_kernel(AssembleArgs<T, D> A
     if (src < 0 || src >= A.n_src_rows) return;
     const int64_t row = A.query_row[i];
     const int64_t slot = A.query_slot ? (int64_t)A.query_slot[i] : -1;
-    if (threadIdx.x < HALF) cs[threadIdx.x] = rope_cs((double)A.query_pos[i], threadIdx.x, D, A.theta);
+    if (threadIdx.x < HALF) cs[threadIdx.x] = rope_cs((double)A.query_pos[i], threadIdx.x, A.freq);
     __syncthreads();
     remap_rows<T, D, kThreads, kUnits, false, false>(A.k_cache, A.v_cache, A.row_stride, A.k_new,
                                                      A.v_new, kvw, src, row, 1, A.hkv,
@@ -112,7 +112,7 @@ __global__ __launch_bounds__(kThreads) void assemble_kernel(AssembleArgs<T, D> A
     const int64_t src = A.probe_src[p];
     if (pr > 0) __syncthreads();  // the previous row's angle table is no longer read
     if (src < 0) continue;  // a query slot (written by that query row's block)
-    if (threadIdx.x < HALF) cs[threadIdx.x] = rope_cs((double)A.probe_delta[p], threadIdx.x, D, A.theta);
+    if (threadIdx.x < HALF) cs[threadIdx.x] = rope_cs((double)A.probe_delta[p], threadIdx.x, A.freq);
     __syncthreads();
     remap_rows<T, D, kThreads, kUnits, false, false>(A.probe_k, A.probe_v, A.probe_stride,
                                                      A.k_pic, A.v_pic, A.pic_stride, src, p, 1,
@@ -159,7 +159,7 @@ hipError_t assemble_t(const AssembleShape& s, const AssemblePtrs& p, hipStream_t
   A.probe_rows_per_block = 1;  // one slot per block: its loads are the only round trip
   A.hq = s.hq;
   A.hkv = s.hkv;
-  A.theta = s.theta;
+  A.freq = rope_freq(s.theta, D);
   const int64_t n_remap = (int64_t)s.n_seg * A.tiles_per_seg;
   const int64_t n_probe_blocks = (s.n_probe + A.probe_rows_per_block - 1) / A.probe_rows_per_block;
   const int64_t blocks = n_remap + s.n_query + n_probe_blocks;

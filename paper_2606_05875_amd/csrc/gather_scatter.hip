@@ -75,7 +75,7 @@ __global__ __launch_bounds__(kThreads) void scatter_kv_kernel(
     T* k_cache, T* v_cache, int64_t n_cache_rows, int64_t cache_stride, const T* k_new,
     const T* v_new, const T* q_new, T* q_out, int64_t n_src_rows, const int32_t* src_idx,
     const int32_t* __restrict__ row_idx, const int32_t* __restrict__ row_pos, int hq, int hkv,
-    double theta) {
+    RopeFreq freq) {
   constexpr int HALF = D / 2;
   constexpr int VEC = Vec16<T>::N;
   constexpr int UPH = HALF / VEC;
@@ -100,7 +100,7 @@ __global__ __launch_bounds__(kThreads) void scatter_kv_kernel(
     ku.load(ks, min(base, nk - 1), nk);
     if (nq > 0) qu.load(qs, min(base, nq - 1), nq);
     if (base == 0) {
-      if (threadIdx.x < HALF) cs[threadIdx.x] = rope_cs((double)row_pos[r], threadIdx.x, D, theta);
+      if (threadIdx.x < HALF) cs[threadIdx.x] = rope_cs((double)row_pos[r], threadIdx.x, freq);
       __syncthreads();
     }
     if (dst_ok) {
@@ -125,7 +125,7 @@ template <typename T, int D>
 __global__ __launch_bounds__(kThreads) void scatter_kv_rows_kernel(
     T* k_cache, T* v_cache, int64_t n_cache_rows, int64_t cache_stride, const T* k_new,
     const T* v_new, int64_t n_src_rows, const int32_t* src_idx, const int32_t* __restrict__ row_idx,
-    const int32_t* __restrict__ row_pos, int64_t n_rows, int hkv, double theta) {
+    const int32_t* __restrict__ row_pos, int64_t n_rows, int hkv, RopeFreq freq) {
   constexpr int HALF = D / 2;
   constexpr int VEC = Vec16<T>::N;
   constexpr int UPH = HALF / VEC;
@@ -160,7 +160,7 @@ __global__ __launch_bounds__(kThreads) void scatter_kv_rows_kernel(
       kb[i] = ld16(ks + koff[i] + HALF);
     }
     if (round == 0) {
-      for (int j = lt; j < HALF; j += TPR) cs[sub][j] = rope_cs((double)row_pos[rc], j, D, theta);
+      for (int j = lt; j < HALF; j += TPR) cs[sub][j] = rope_cs((double)row_pos[rc], j, freq);
       __syncthreads();
     }
     if (!ok) continue;
@@ -189,18 +189,19 @@ hipError_t scatter_t(void* k_cache, void* v_cache, int64_t n_cache_rows, int64_t
                      int64_t n_src_rows, const int32_t* src_idx, int64_t n_rows,
                      const int32_t* row_idx, const int32_t* row_pos, int hq, int hkv,
                      double theta, hipStream_t stream) {
+  const RopeFreq freq = rope_freq(theta, D);
   if (!q_new && !q_out) {
     constexpr int RPB = kThreads / 64;
     scatter_kv_rows_kernel<T, D><<<dim3((unsigned)((n_rows + RPB - 1) / RPB)), kThreads, 0, stream>>>(
         static_cast<T*>(k_cache), static_cast<T*>(v_cache), n_cache_rows, cache_stride,
         static_cast<const T*>(k_new), static_cast<const T*>(v_new), n_src_rows, src_idx, row_idx,
-        row_pos, n_rows, hkv, theta);
+        row_pos, n_rows, hkv, freq);
     return hipGetLastError();
   }
   scatter_kv_kernel<T, D><<<dim3((unsigned)n_rows), kThreads, 0, stream>>>(
       static_cast<T*>(k_cache), static_cast<T*>(v_cache), n_cache_rows, cache_stride,
       static_cast<const T*>(k_new), static_cast<const T*>(v_new), static_cast<const T*>(q_new),
-      static_cast<T*>(q_out), n_src_rows, src_idx, row_idx, row_pos, hq, hkv, theta);
+      static_cast<T*>(q_out), n_src_rows, src_idx, row_idx, row_pos, hq, hkv, freq);
   return hipGetLastError();
 }
 

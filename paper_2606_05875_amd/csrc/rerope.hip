@@ -25,7 +25,7 @@ __global__ __launch_bounds__(kThreads) void rerope_kernel(
     int hkv, int64_t out_stride, int64_t in_stride, int rows_per_block,
     const int32_t* __restrict__ seg_start,
     const int32_t* __restrict__ seg_len, const int32_t* __restrict__ seg_delta,
-    const int32_t* __restrict__ src_start, double theta) {
+    const int32_t* __restrict__ src_start, RopeFreq freq) {
   constexpr int HALF = D / 2;
   __shared__ float2 cs[HALF];
 
@@ -40,7 +40,7 @@ __global__ __launch_bounds__(kThreads) void rerope_kernel(
   remap_rows<T, D, kThreads, kUnitsPerThread, kStreamIn, true>(
       k_out, vdst, out_stride, k_in, v_in, in_stride, src0, dst0, min(rows_per_block, len - r0),
       hkv, n_in_rows, n_out_rows, cs, [&] {
-        if (threadIdx.x < HALF) cs[threadIdx.x] = rope_cs((double)seg_delta[s], threadIdx.x, D, theta);
+        if (threadIdx.x < HALF) cs[threadIdx.x] = rope_cs((double)seg_delta[s], threadIdx.x, freq);
         __syncthreads();
       });
 }
@@ -61,7 +61,7 @@ hipError_t launch_t(void* k_out, const void* k_in, void* v_out, const void* v_in
   kern<<<grid, kThreads, 0, stream>>>(
       static_cast<T*>(k_out), static_cast<const T*>(k_in), static_cast<T*>(v_out),
       static_cast<const T*>(v_in), n_out_rows, n_in_rows, hkv, out_stride, in_stride, rpb, seg_start,
-      seg_len, seg_delta, src_start, theta);
+      seg_len, seg_delta, src_start, rope_freq(theta, D));
   return hipGetLastError();
 }
 
@@ -69,10 +69,10 @@ hipError_t launch_t(void* k_out, const void* k_in, void* v_out, const void* v_in
 // forms for offset pos[i] and frequency j (float64 angle, rounded to float32)
 __global__ __launch_bounds__(64) void rope_table_kernel(float2* __restrict__ table,
                                                         const int32_t* __restrict__ pos, int d,
-                                                        double theta) {
+                                                        RopeFreq freq) {
   const int64_t i = blockIdx.x;
   if ((int)threadIdx.x < d / 2)
-    table[i * (d / 2) + threadIdx.x] = rope_cs((double)pos[i], threadIdx.x, d, theta);
+    table[i * (d / 2) + threadIdx.x] = rope_cs((double)pos[i], threadIdx.x, freq);
 }
 
 }  // namespace
@@ -81,7 +81,7 @@ hipError_t launch_rope_table(float* table, const int32_t* pos, int64_t n, int d,
                              hipStream_t stream) {
   if (n == 0) return hipSuccess;
   rope_table_kernel<<<dim3((unsigned)n), 64, 0, stream>>>(reinterpret_cast<float2*>(table), pos, d,
-                                                          theta);
+                                                          rope_freq(theta, d));
   return hipGetLastError();
 }
 
