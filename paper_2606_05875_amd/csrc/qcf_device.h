@@ -89,7 +89,7 @@ __device__ __forceinline__ float2 rope_cs(double pos, int j, const RopeFreq& fr)
   double x = pos;
 #pragma unroll
   for (int i = 0; i < 6; ++i) x = (j >> i) & 1 ? x * fr.f[i] : x;
-  if (!(fabs(x) < 0x1p52)) x = 0.0;
+  if (!(fabs(x) < 0x1p52)) x -= x;  // no digit after the point is left: 0; infinity, NaN: NaN
   const double k = rint(x * 0x1.45f306dc9c883p-1);  // 2 / pi
   double r = fma(-k, 0x1.921fb54442d18p+0, x);
   r = fma(-k, 0x1.1a62633145c07p-54, r);
