@@ -8,9 +8,9 @@
 // fastest, with the splits chosen for about 512 blocks:
 //   stats   : each of the 8 waves holds 32 query vectors of one KV-head group
 //             in registers; the split's keys pass through LDS (128 at a time,
-//             the next ones prefetched into registers) in 32-key products,
-//             and every vector keeps an online (max, sum); the split's base-2
-//             log-sum-exp is written.
+//             the next ones prefetched into registers; long splits: a ring of
+//             64-key stages) in 32-key products, and every vector keeps an
+//             online (max, sum); the split's base-2 log-sum-exp is written.
 //   columns : the same tiles again.  Each vector's log-sum-exp over all splits
 //             is merged once per block (its partials loaded together, folded
 //             in split order); the logits are recomputed and each key's
@@ -37,6 +37,7 @@
 
 #include <algorithm>
 
+#include "qcf_attn.h"
 #include "qcf_device.h"
 #include "qcf_launch.h"
 
@@ -47,6 +48,9 @@ constexpr int kThreads = 256;      // final pass
 constexpr int kW = 8;              // bf16 path: waves per block
 constexpr int kQvTile = 32 * kW;   // query vectors per block
 constexpr int kChunkKeys = 128;    // keys staged in LDS at a time
+constexpr int kRing = 4;           // long splits: LDS stages of the key ring
+constexpr int kRingKeys = 64;      // keys per stage
+constexpr int kRingSplit = 512;    // shortest split that takes the ring
 constexpr int kMaxSplits = 64;     // key splits per query tile
 constexpr int kPassBlocks = 512;   // blocks aimed for when choosing the splits
 constexpr int kCUs = 256;          // compute units of MI355X
@@ -95,8 +99,6 @@ WsLayout ws_layout(const ProbeShape& s) {
   w.total = w.col_off + align256(nb * (size_t)w.n_qt * s.max_ctx_len * sizeof(float));
   return w;
 }
-
-__device__ __forceinline__ bf16x8 as_bf16x8(const uint4& v) { return __builtin_bit_cast(bf16x8, v); }
 
 __device__ __forceinline__ float2 combine_ml(float2 a, float2 b) {
   const float m = fmaxf(a.x, b.x);
@@ -234,11 +236,6 @@ __global__ __launch_bounds__(kW * 64) void scores_pass_bf16(
 #pragma unroll
     for (int v = 0; v < 16; ++v) lse_v[v] = lse_l[32 * w + 8 * (v >> 2) + 4 * hi + (v & 3)];
   }
-  // Q has to be there before the loop: the compiler's wait for it at the products would count
-  // the next chunk's loads too, so that every chunk waited for them (128 query rows, 64/8
-  // heads, 32768 keys: scores and selection 176-180 -> 172.5 us)
-#pragma unroll
-  for (int st = 0; st < D / 16; ++st) asm volatile("" : "+v"(qreg[st]));
   float m = -INFINITY, ls = 0.f;
   for (int c0 = key_lo; c0 < key_hi; c0 += kChunkKeys) {
     if (c0 > key_lo) __syncthreads();  // the previous chunk (and its sums) are no longer read
@@ -341,6 +338,255 @@ __global__ __launch_bounds__(kW * 64) void scores_pass_bf16(
   }
 }
 
+// ---------------------------------------------------------------- bf16 passes, long splits
+// The two passes for splits of 512 keys and more (stored keys only): the same tiles, sums and
+// order, so the same bits.  Bound: a wave's vector instructions and products in turn -- the
+// pass above issues a group's 8 dependent products in a burst and then its 16 exponentials,
+// and on 4 waves per SIMD its time is the sum of both (86.7 us for 128 query rows, 64/8 heads,
+// 32768 keys; 60 with one product of eight, 73 without the exponentials).  Here S of the next
+// group is fenced in between the exponentials of this one, product by product, and the keys
+// come through a 4-stage LDS ring (64 keys, buffer loads into LDS three stages ahead) instead
+// of registers, which leaves room for both score tiles at two blocks per CU.  Scores and
+// selection at that size 180 -> 170 us, a ragged 16-request batch 322 -> 287 us.  With 128-key
+// stages (one block per CU) 188 and 371 us: nothing hides a block's start.  Shorter splits
+// gain nothing (10 x 512 tokens: 24.9 us either way) and keep the pass above, as do keys
+// rotated on the fly.
+template <int D, bool kCols>
+__global__ __launch_bounds__(kW * 64, 4) void scores_ring_bf16(  // (4 waves per SIMD: two blocks per CU)
+    float* __restrict__ part, float* __restrict__ colp, const uint16_t* __restrict__ q,
+    int64_t n_q_rows, const uint16_t* __restrict__ k, int64_t n_kv_rows, int64_t k_stride,
+    const int32_t* __restrict__ cu_q, const int32_t* __restrict__ cu_kv,
+    const int32_t* __restrict__ ctx_len, int hq, int hkv, int lg, int n_qt, int n_splits,
+    int split_keys, int max_qv, int max_ctx, float scale2) {
+  constexpr int CPR = D / 8;                // 16-byte pieces per K row
+  constexpr int RB = D * 2;                 // bytes per LDS row
+  constexpr int ST = kRingKeys * RB;        // bytes per stage
+  constexpr int RPS = 64 / CPR;             // rows per 64-lane transfer
+  constexpr int SPW = kRingKeys / RPS / kW;  // transfers per wave and chunk
+  constexpr int SPL = kMaxSplits / 2;       // splits per lane in the merge
+  __shared__ __attribute__((aligned(1024))) uint8_t k_lds[kRing * ST];
+  __shared__ float lse_l[kCols ? kQvTile : 1];
+  __shared__ float red[kCols ? 3 : 1][kCols ? kW : 1][kCols ? kRingKeys : 1];
+
+  // block -> (KV head, query tile, split, request) with the head fastest:
+  // blocks are dealt to the XCDs in turn, so with 8 KV heads every block of a
+  // head runs on one XCD and its Q and split statistics are shared in that L2
+  const int g = blockIdx.x % hkv;
+  const int rest = blockIdx.x / hkv;
+  const int qt = rest % n_qt, split = (rest / n_qt) % n_splits, b = rest / (n_qt * n_splits);
+  const int64_t q0 = cu_q[b];
+  const int nqv = min((cu_q[b + 1] - (int)q0) << lg, max_qv);
+  if (qt * kQvTile >= nqv) return;
+  const int64_t k0 = cu_kv[b];
+  const int N = ctx_len[b];
+  const int key_lo = split * split_keys;
+  const int key_hi = min(N, key_lo + split_keys);
+  if (kCols && key_lo >= key_hi) return;  // no keys: no columns (an empty split's statistics are still written)
+  const int w = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int l = threadIdx.x & 63, lq = l & 31, hi = l >> 5;
+  const int qv = qt * kQvTile + 32 * w + lq;
+  const int64_t qrow = q0 + (qv >> lg);
+  const bool valid = qv < nqv && qrow < n_q_rows;
+  const bool live = __ballot(valid) != 0;  // the wave has a real query vector
+  const int head = g * (1 << lg) + (qv & ((1 << lg) - 1));
+
+  // Keys arrive by buffer loads with an LDS destination, three chunks ahead; the descriptor ends
+  // at the last key that exists, past it rows read as zeros (keys past the split are masked
+  // where their products are used).  Chunk c of LDS row r sits at c ^ (r % 16) (D = 64: c ^ (r /
+  // 2 % 8)): conflict-free fragment reads without padding.
+  const uint32_t row_b = (uint32_t)(k_stride * 2);
+  const int n_chunk = key_lo < key_hi ? (key_hi - key_lo + kRingKeys - 1) / kRingKeys : 0;
+  const int64_t kfirst = min(k0 + key_lo, n_kv_rows - 1);
+  const int64_t kleft = min((int64_t)key_hi - key_lo, n_kv_rows - kfirst);
+  const int dr = RPS * w + l / CPR, dc = l % CPR;  // transfer i fills rows dr + RPS kW i
+  const uint32_t koff = (uint32_t)dr * row_b + (dc ^ (D == 128 ? dr & 15 : (dr >> 1) & 7)) * 16;
+  const uint32_t k_base = lds_addr(k_lds);
+  const uint16_t* kb = k + kfirst * k_stride + (int64_t)g * D;
+  auto issue = [&](int c) {
+    const int64_t rows = min(kleft - (int64_t)c * kRingKeys, (int64_t)kRingKeys);
+    const i32x4 rk = make_rsrc(kb + (rows > 0 ? (int64_t)c * kRingKeys * k_stride : 0),
+                               rows > 0 ? (uint32_t)(rows - 1) * row_b + RB : 0u);
+#pragma unroll
+    for (int i = 0; i < SPW; ++i) {
+      const uint32_t soff = (uint32_t)(RPS * kW * i) * row_b;
+      dma16(rk, koff + soff, k_base + (uint32_t)((c & (kRing - 1)) * ST + (w + kW * i) * 1024));
+    }
+  };
+  if (n_chunk > 0) {
+    issue(0);
+    issue(1);
+    issue(2);
+  }
+  bf16x8 qreg[D / 16];
+  {
+    const uint16_t* qp = q + min(qrow, n_q_rows - 1) * (int64_t)hq * D + (int64_t)head * D + 8 * hi;
+#pragma unroll
+    for (int st = 0; st < D / 16; ++st) qreg[st] = as_bf16x8(ld16(qp + 16 * st));
+  }
+  float lse_v[kCols ? 16 : 1];
+  if (kCols) {
+    // the vector's base-2 log-sum-exp over every split: lanes l (even splits)
+    // and l^32 (odd splits) fold theirs in split order, then even + odd; its
+    // padding rows get a reference that sends every exponential to 0
+    // (branch-free, so every load is issued before the first one is used;
+    // an empty split's -inf and a masked slot count as a floor with weight 0)
+    // loads are unconditional, from clamped rows: a load under a lane condition gets a wait of its own
+    const float* pg = part + (int64_t)(b * hkv + g) * n_splits * max_qv + min(qv, max_qv - 1);
+    float x[SPL];
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) x[j] = pg[min(2 * j + hi, n_splits - 1) * max_qv];
+    asm volatile("" ::: "memory");  // all of them in flight before the first is used
+    constexpr float kFloor = -1e30f;
+    float mx = kFloor, ls = 0.f;
+#pragma unroll
+    for (int j = 0; j < SPL; ++j) {
+      const bool ok = valid && 2 * j + hi < n_splits && x[j] > kFloor;
+      const float xj = ok ? x[j] : kFloor;
+      const float mn = fmaxf(mx, xj);
+      ls = ls * __builtin_amdgcn_exp2f(mx - mn) + (ok ? __builtin_amdgcn_exp2f(xj - mn) : 0.f);
+      mx = mn;
+    }
+    if (ls == 0.f) mx = -INFINITY;
+    const float2 mine = make_float2(mx, ls);
+    const float2 other = make_float2(__shfl_xor(mx, 32, 64), __shfl_xor(ls, 32, 64));
+    const float2 ml = hi == 0 ? combine_ml(mine, other) : combine_ml(other, mine);
+    if (hi == 0) lse_l[32 * w + lq] = (valid && ml.y > 0.f) ? ml.x + __builtin_amdgcn_logf(ml.y) : 1e30f;
+    __syncthreads();
+    // S layout: value v of a lane belongs to query vector 8(v>>2)+4hi+(v&3) of the wave
+#pragma unroll
+    for (int v = 0; v < 16; ++v) lse_v[v] = lse_l[32 * w + 8 * (v >> 2) + 4 * hi + (v & 3)];
+  }
+  // Q has to be there before the loop: the compiler's wait for it at the products would count
+  // later loads too
+#pragma unroll
+  for (int st = 0; st < D / 16; ++st) asm volatile("" : "+v"(qreg[st]));
+  float m = -INFINITY, ls = 0.f;
+  constexpr int NS = D / 16;   // products per group
+  constexpr int EG = 16 / NS;  // elements of a group per product
+  const int ky = D == 128 ? lq & 15 : (lq >> 1) & 7;
+  const int krd = lq * RB + (hi ^ (ky & 1)) * 16 + (ky >> 1) * 32;
+  auto frag = [&](const uint8_t* kl, int st) { return as_bf16x8(ld16(kl + (krd ^ (st << 5)))); };
+  auto mfma = [&](const bf16x8& a, int st, const f32x16& c) {
+    return kCols ? __builtin_amdgcn_mfma_f32_32x32x16_bf16(qreg[st], a, c, 0, 0, 0)
+                 : __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, qreg[st], c, 0, 0, 0);
+  };
+  // exponential argument of value v: statistics (S^T: key 8(v>>2)+4hi+(v&3) of the group, the
+  // lane's vector) relative to the running reference, columns (S: the lane's key, vector
+  // 8(v>>2)+4hi+(v&3)) to the vector's log-sum-exp
+  auto arg = [&](const f32x16& s, int v, float nm) {
+    return fmaf(s[v], scale2, kCols ? -lse_v[kCols ? v : 0] : nm);
+  };
+  // S(next) beside the exponentials of S(cur): groups fenced with sched_barrier, one product each,
+  // with its K fragment read PF groups ahead, so the matrix cores and the vector ALUs run
+  // side by side inside a wave; returns the sum of the exponentials.
+  auto fused = [&](const uint8_t* kl, f32x16& sn, const f32x16& sc, float nm) {
+    constexpr int PF = 4;
+    bf16x8 a[NS];
+#pragma unroll
+    for (int i = 0; i < PF; ++i) a[i] = frag(kl, i);
+    float x[16], p[16], sum = 0.f;
+#pragma unroll
+    for (int v = 0; v < EG; ++v) x[v] = arg(sc, v, nm);
+#pragma unroll
+    for (int i = 0; i < NS; ++i) {
+      __builtin_amdgcn_sched_barrier(0);
+      if (i + PF < NS) a[i + PF] = frag(kl, i + PF);
+      sn = mfma(a[i], i, i == 0 ? f32x16{} : sn);
+#pragma unroll
+      for (int v = EG * (i + 1); v < EG * (i + 2) && v < 16; ++v) x[v] = arg(sc, v, nm);
+#pragma unroll
+      for (int v = EG * i; v < EG * (i + 1); ++v) {
+        p[v] = __builtin_amdgcn_exp2f(x[v]);
+        asm volatile("" : "+v"(p[v]));  // stays in its group
+      }
+      if (i > 0) {
+#pragma unroll
+        for (int v = EG * (i - 1); v < EG * i; ++v) sum += p[v];
+      }
+    }
+    __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+    for (int v = EG * (NS - 1); v < 16; ++v) sum += p[v];
+    return sum;
+  };
+  f32x16 s0, s1;
+  auto colsum = [&](int c) {  // the column sums of chunk c over the waves, after a barrier
+    if constexpr (kCols) {
+      const int t = threadIdx.x, key = key_lo + c * kRingKeys + t;
+      if (t < kRingKeys && key < key_hi) {
+        float acc = 0.f;
+#pragma unroll
+        for (int ww = 0; ww < kW; ++ww) acc += red[c % 3][ww][t];
+        colp[((int64_t)(b * hkv + g) * n_qt + qt) * max_ctx + key] = acc;
+      }
+    }
+  };
+  auto meet = [&]() {  // the next chunk has landed (two younger ones may be on their way); the block meets
+    asm volatile("" ::: "memory");
+    wait_vm_lgkm0<2 * SPW>();
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+  };
+  if (kCols && !live) {  // a wave without real query vectors adds nothing: it only loads and meets
+#pragma unroll
+    for (int i = 0; i < (kCols ? 3 : 0); ++i) red[i][w][l] = 0.f;
+  }
+  if (n_chunk > 0) {
+    meet();
+    if (live) {
+#pragma unroll
+      for (int st = 0; st < NS; ++st) s0 = mfma(frag(k_lds, st), st, st == 0 ? f32x16{} : s0);
+    }
+  }
+  // One 32-key group: its exponentials, beside the products of the wave's next group at kl.
+  auto group = [&](int c, int kg, const uint8_t* kl, f32x16& sc, f32x16& sn) {
+    const int kt0 = key_lo + c * kRingKeys + kg * 32;
+    if constexpr (!kCols) {
+      if (kt0 + 32 > key_hi) {  // keys past the split are masked
+#pragma unroll
+        for (int v = 0; v < 16; ++v)
+          if (kt0 + 8 * (v >> 2) + 4 * hi + (v & 3) >= key_hi) sc[v] = -INFINITY;
+      }
+      float mt = -INFINITY;
+#pragma unroll
+      for (int v = 0; v < 16; ++v) mt = fmaxf(mt, sc[v]);
+      const float mn = fmaxf(m, mt * scale2);
+      const float sum = fused(kl, sn, sc, -mn);
+      ls = mn != -INFINITY ? ls * __builtin_amdgcn_exp2f(m - mn) + sum : ls;
+      m = mn;
+    } else {
+      const float sum = fused(kl, sn, sc, 0.f);
+      const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(sum), __float_as_uint(sum), false, false);
+      if (hi == 0) red[c % 3][w][kg * 32 + lq] = __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+    }
+  };
+  // A chunk's two groups, each beside the products of the next one; the second multiplies into
+  // the next chunk (past the last: zero rows, unused), so the block meets before it.
+  for (int c = 0; c < n_chunk; ++c) {
+    // (both stages' addresses up here: formed at their uses, the D = 128 statistics spill 20 registers)
+    const uint8_t* kc = k_lds + (c & (kRing - 1)) * ST;
+    const uint8_t* kn = k_lds + ((c + 1) & (kRing - 1)) * ST;
+    issue(c + 3);  // into the stage of chunk c - 1, last read before the last barrier
+    constexpr int GB = 32 * RB;  // LDS bytes of a group
+    if (live) group(c, 0, kc + GB, s0, s1);
+    meet();
+    if (c > 0) colsum(c - 1);
+    if (live) group(c, 1, kn, s1, s0);
+  }
+  wait_vm_lgkm0<0>();  // the last (zero-row) transfers, before the LDS is released
+  if constexpr (kCols) {
+    __syncthreads();
+    if (n_chunk > 0) colsum(n_chunk - 1);
+  } else {
+    // lanes l and l^32 hold disjoint keys of the same query vector; the split's base-2
+    // log-sum-exp is max + log2(sum) (-inf: no keys)
+    const float2 ml = combine_ml(make_float2(m, ls), make_float2(__shfl_xor(m, 32, 64), __shfl_xor(ls, 32, 64)));
+    if (valid && hi == 0)
+      part[((int64_t)(b * hkv + g) * n_splits + split) * max_qv + qv] =
+          ml.y > 0.f ? ml.x + __builtin_amdgcn_logf(ml.y) : -INFINITY;
+  }
+}
+
 // ---------------------------------------------------------------- bf16 final
 // scores[t] (+)= the column sums of every (KV head, query tile) of the request
 // that has query vectors, head-major
@@ -410,17 +656,29 @@ hipError_t launch_probe_scores(float* scores, int accumulate, const void* q, int
   scores_pass_bf16<D, C, R><<<grid, kW * 64, 0, stream>>>(                                         \
       part, colp, qb, n_q_rows, kb, n_kv_rows, k_row_stride, rot.row, tab, n_rot, cu_q, cu_kv,     \
       ctx_len, s.hq, s.hkv, lg, w.n_qt, w.n_splits, w.split_keys, w.max_qv, s.max_ctx_len, scale2)
-#define QCF_PASSES(D, R) \
-  do {                   \
-    QCF_PASS(D, false, R); \
-    QCF_PASS(D, true, R);  \
+#define QCF_RING(D, C)                                                                             \
+  scores_ring_bf16<D, C><<<grid, kW * 64, 0, stream>>>(                                            \
+      part, colp, qb, n_q_rows, kb, n_kv_rows, k_row_stride, cu_q, cu_kv, ctx_len, s.hq, s.hkv,    \
+      lg, w.n_qt, w.n_splits, w.split_keys, w.max_qv, s.max_ctx_len, scale2)
+#define QCF_PASSES(D, R)     \
+  do {                       \
+    if (!R && ring) {        \
+      QCF_RING(D, false);    \
+      QCF_RING(D, true);     \
+    } else {                 \
+      QCF_PASS(D, false, R); \
+      QCF_PASS(D, true, R);  \
+    }                        \
   } while (0)
+    // (a stage's byte offsets are 32-bit)
+    const bool ring = w.split_keys >= kRingSplit && k_row_stride * 2 * kRingKeys < (int64_t)1 << 31;
     if (s.d == 64) {
       if (rt) QCF_PASSES(64, true); else QCF_PASSES(64, false);
     } else {
       if (rt) QCF_PASSES(128, true); else QCF_PASSES(128, false);
     }
 #undef QCF_PASSES
+#undef QCF_RING
 #undef QCF_PASS
   }
   if (sel && sel->max_seg_len <= 1024) {
