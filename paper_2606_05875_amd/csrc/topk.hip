@@ -3,13 +3,13 @@
 // over the whole context).
 //
 // One block per segment.  Scores become order-preserving uint32 keys (larger
-// score -> larger key, -0 == +0).  A most-significant-digit radix select (4
-// passes of 8 bits, LDS histograms) finds the key tau of the k-th largest
-// score and how many of the keys equal to tau are still needed.  The chosen
-// rows are then written in index order, taking keys > tau and the
-// lowest-index keys == tau, so the output is ascending and ties go to the
-// lower row -- exactly the order (score desc, index asc).  The result is
-// bit-exact and independent of scheduling.
+// score -> larger key, -0 == +0).  A most-significant-digit radix select (8
+// bits a pass, LDS histograms) finds the key tau of the k-th largest score and
+// how many of the keys equal to tau are still needed.  The chosen rows are
+// then written in index order, taking keys > tau and the lowest-index keys ==
+// tau, so the output is ascending and ties go to the lower row -- exactly the
+// order (score desc, index asc).  The result is bit-exact and independent of
+// scheduling.
 //
 // Segments of up to 65536 keys (a whole long request in global mode) stay in
 // registers: key i lives in thread i % NT, slot i / NT, so one coalesced read
@@ -18,6 +18,15 @@
 // (slot, wave) order -- which is index order -- and the lane's position in
 // its ballot.  Longer segments take the fallback kernel, which re-reads the
 // scores from memory in every pass.
+//
+// In registers the select is bound by the histogram: lanes that add to one bin
+// go one after another, and the scores of a segment share their sign and most
+// of their exponent, so digits taken from bit 31 down put nearly every key of
+// the first pass in one or two bins.  The digits therefore start at the first
+// bit in which the segment's keys differ (one OR of the keys and one of their
+// complements), and the passes end as soon as all keys of the k-th one's bin
+// are taken: 16 requests of about 12000 scores 25.7 -> 13.2 us, 10 chunks of 512
+// with their column sums 8.6 -> 6.4.
 #include "qcf_device.h"
 #include "qcf_launch.h"
 
@@ -54,8 +63,8 @@ __device__ __forceinline__ uint32_t block_prefix(bool pred, uint32_t* wave_tot, 
 }
 
 // After a histogram pass: the digit of the k-th largest among the keys that
-// match the prefix so far (hist[d] = their count with digit d) and how many
-// keys with a larger digit precede it.  Run by one whole wave.
+// match the prefix so far (hist[d] = their count with digit d), how many keys
+// with a larger digit precede it and how many have it.  Run by one whole wave.
 __device__ __forceinline__ void digit_search(const uint32_t* hist, int remaining, uint32_t* sh) {
   const int lane = threadIdx.x & 63;
   // lane l owns digits 255-4l .. 252-4l (descending digit order)
@@ -80,6 +89,7 @@ __device__ __forceinline__ void digit_search(const uint32_t* hist, int remaining
       if (above + c[e] >= (uint32_t)remaining) {
         sh[0] = 255u - 4u * lane - e;
         sh[1] = above;
+        sh[2] = c[e];
         break;
       }
       above += c[e];
@@ -116,6 +126,19 @@ __device__ void radix_select(KeyAt key_at, int n, int k, uint32_t* hist, uint32_
 }
 
 // ---------------------------------------------------------------- register path
+template <int kRor>
+__device__ __forceinline__ uint32_t or_row_rotated(uint32_t x) {
+  return x | (uint32_t)__builtin_amdgcn_update_dpp(0, (int)x, 0x120 + kRor, 0xf, 0xf, false);
+}
+__device__ __forceinline__ uint32_t wave_or(uint32_t x) {
+  x = or_row_rotated<8>(x);
+  x = or_row_rotated<4>(x);
+  x = or_row_rotated<2>(x);
+  x = or_row_rotated<1>(x);
+  x |= __shfl_xor(x, 16, 64);
+  return x | __shfl_xor(x, 32, 64);
+}
+
 // In place: cells[0 .. nc) -> their exclusive prefix sums.  Run by one wave.
 template <int NC>
 __device__ __forceinline__ void scan_cells(uint32_t* cells) {
@@ -159,9 +182,10 @@ __global__ __launch_bounds__(NT) void topk_reg_kernel(
   static_assert(NT >= 256 && NT % 64 == 0 && KPT >= 1 && KPT <= 64, "block shape");
   constexpr int NW = NT / 64;
   constexpr int NC = KPT * NW;  // (slot, wave) cells, slot-major = index order
-  __shared__ uint32_t hist[256];
+  __shared__ uint32_t hist[2][256];
   __shared__ uint32_t cells[NC];
-  __shared__ uint32_t sh[2];
+  __shared__ uint32_t sh[2][3];
+  __shared__ uint2 bits[NW];
 
   const int s = blockIdx.x;
   const int64_t start = seg_start[s];
@@ -237,52 +261,75 @@ __global__ __launch_bounds__(NT) void topk_reg_kernel(
   if (k > n) k = n;
   if (o < 0 || o + k > n_out) return;
 
-  const bool take_all = (k == n);
-  uint32_t tau = 0u;
-  int remaining = k;
-  if (!take_all) {
-    uint32_t prefix = 0u, mask = 0u;
-    for (int shift = 24; shift >= 0; shift -= 8) {
-      if (tid < 256) hist[tid] = 0u;
-      __syncthreads();
-#pragma unroll
-      for (int j = 0; j < KPT; ++j)
-        if ((key[j] & mask) == prefix) atomicAdd(&hist[(key[j] >> shift) & 255u], 1u);
-      __syncthreads();
-      if (w == 0) digit_search(hist, remaining, sh);
-      __syncthreads();
-      prefix |= sh[0] << shift;
-      remaining -= (int)sh[1];
-      mask |= 255u << shift;
-      __syncthreads();  // sh and hist are rewritten by the next pass
-    }
-    tau = prefix;
-  }
-
   // which slots are chosen: keys > tau, and keys == tau whose rank among the
   // keys == tau (index order) is below `remaining`
   uint64_t sel = 0;
-  if (take_all) {
+  if (k == n) {
 #pragma unroll
     for (int j = 0; j < KPT; ++j)
       if (tid + j * NT < n) sel |= 1ull << j;
   } else {
+    uint32_t ones = 0u, zeros = 0u;
 #pragma unroll
     for (int j = 0; j < KPT; ++j) {
-      const uint64_t m = __ballot(key[j] == tau);
-      if (lane == 0) cells[j * NW + w] = (uint32_t)__popcll(m);
+      const bool in = tid + j * NT < n;
+      ones |= in ? key[j] : 0u;
+      zeros |= in ? ~key[j] : 0u;
     }
-    __syncthreads();
-    if (w == 0) scan_cells<NC>(cells);
+    ones = wave_or(ones);
+    zeros = wave_or(zeros);
+    if (lane == 0) bits[w] = make_uint2(ones, zeros);
+    if (tid < 256) hist[0][tid] = hist[1][tid] = 0u;
     __syncthreads();
 #pragma unroll
-    for (int j = 0; j < KPT; ++j) {
-      const bool eq = key[j] == tau;
-      const uint64_t m = __ballot(eq);
-      const uint32_t rank = cells[j * NW + w] + lanes_below(m);
-      if (key[j] > tau || (eq && rank < (uint32_t)remaining)) sel |= 1ull << j;
+    for (int ww = 0; ww < NW; ++ww) {
+      ones |= bits[ww].x;
+      zeros |= bits[ww].y;
     }
-    __syncthreads();  // cells are rewritten below
+    const uint32_t diff = __builtin_amdgcn_readfirstlane(ones & zeros);
+    int open = diff ? 32 - __clz((int)diff) : 0;  // low bits not yet known of tau
+    uint32_t mask = diff ? ~(0xffffffffu >> (32 - open)) : 0xffffffffu;
+    uint32_t prefix = __builtin_amdgcn_readfirstlane(ones) & mask;
+    int remaining = k;  // how many of the keys matching the prefix are still to be taken
+    bool whole = false;  // all of them
+    // the histograms alternate: one is cleared while the other is searched
+    for (int p = 0; open > 0 && !whole; p ^= 1) {
+      const int shift = max(open - 8, 0);
+#pragma unroll
+      for (int j = 0; j < KPT; ++j)
+        if ((key[j] & mask) == prefix) atomicAdd(&hist[p][(key[j] >> shift) & 255u], 1u);
+      __syncthreads();
+      if (w == 0) digit_search(hist[p], remaining, sh[p]);
+      if (tid < 256) hist[p ^ 1][tid] = 0u;
+      __syncthreads();
+      prefix |= __builtin_amdgcn_readfirstlane(sh[p][0]) << shift;
+      remaining -= (int)__builtin_amdgcn_readfirstlane(sh[p][1]);
+      whole = (int)__builtin_amdgcn_readfirstlane(sh[p][2]) == remaining;
+      mask |= 255u << shift;
+      open = shift;
+    }
+    if (whole) {
+#pragma unroll
+      for (int j = 0; j < KPT; ++j)
+        if ((key[j] & mask) >= prefix) sel |= 1ull << j;
+    } else {  // tau is known to the last bit
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) {
+        const uint64_t m = __ballot(key[j] == prefix);
+        if (lane == 0) cells[j * NW + w] = (uint32_t)__popcll(m);
+      }
+      __syncthreads();
+      if (w == 0) scan_cells<NC>(cells);
+      __syncthreads();
+#pragma unroll
+      for (int j = 0; j < KPT; ++j) {
+        const bool eq = key[j] == prefix;
+        const uint64_t m = __ballot(eq);
+        const uint32_t rank = cells[j * NW + w] + lanes_below(m);
+        if (key[j] > prefix || (eq && rank < (uint32_t)remaining)) sel |= 1ull << j;
+      }
+      __syncthreads();  // cells are rewritten below
+    }
   }
   // output slots of the chosen keys, in index order
 #pragma unroll
@@ -317,7 +364,7 @@ __global__ __launch_bounds__(kThreads) void select_topk_kernel(
     const int32_t* __restrict__ seg_req, const int32_t* __restrict__ req_base, int n_req) {
   __shared__ uint32_t hist[256];
   __shared__ uint32_t wave_tot[kWaves];
-  __shared__ uint32_t sh[2];
+  __shared__ uint32_t sh[3];
 
   const int s = blockIdx.x;
   const int64_t start = seg_start[s];
