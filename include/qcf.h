@@ -348,7 +348,9 @@ qcf_status qcf_probe_scores_select_noalloc(float* scores, int accumulate, const 
  *        steps of all its row tiles evenly over a fixed grid of blocks; the
  *        workspace then holds the work plan and the partial results of row tiles
  *        cut between two blocks, which a second kernel merges in a fixed order
- *        (deterministic).  A bf16 call without kv_pos over one request with at
+ *        (deterministic).  A bf16 call with very few query vectors over long key
+ *        ranges cuts the ranges over blocks and merges their partial results from
+ *        the workspace in the same way; without room for them it runs uncut.  A bf16 call without kv_pos over one request with at
  *        least four row tiles per compute unit hands the tiles out from work
  *        counters in the workspace, which the call resets itself (by a kernel on
  *        the same stream); each tile is still computed whole by one block, so the
