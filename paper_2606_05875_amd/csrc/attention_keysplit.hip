@@ -321,7 +321,10 @@ static void unit_counts(const AttnShape& s, int64_t n_rows, int64_t n_kv_rows, i
 // kernel against the shared-tile one).
 //  * Explicit key positions: 64 units x 35 tiles 14.5 / 65.6; 64 x 322 30 / 548; 256 x 36
 //    16.1 / 66.6; 256 x 1028 228 / 1748; 2048 x 130 110 / 172; 2048 x 9 31.7 / 31.3;
-//    4096 x 9 82 / 57; 4096 x 66 315 / 276.
+//    4096 x 9 82 / 57; 4096 x 66 315 / 276.  Short ranges at head size 128, where blocks that
+//    no longer fit the chip at once start for little work: 512 x 3 11.8 / 12.3, 720 x 6 17.7 /
+//    16.7, 720 x 8 20.1 / 19.8, 1024 x 3 15.5 / 13.5, 720 x 12 24.9 / 26.5 (head size 64, smaller
+//    blocks: 1024 x 3 7.7 / 10.3).
 //  * Causal rows (half the tiles are visible on average; their shared-tile kernel adapts its
 //    grid): units x tiles at head size 128 (with the re-positioning and scatter before it)
 //    138 x 18 21 / 38; 523 x 50 45 / 49; 1024 x 16 37 / 41; 2560 x 4 46 / 49; 1152 x 34 60 /
@@ -329,7 +332,10 @@ static void unit_counts(const AttnShape& s, int64_t n_rows, int64_t n_kv_rows, i
 bool use_keysplit(const AttnShape& s, int64_t n_rows, int64_t n_kv_rows, bool kv_pos) {
   int64_t per_req, units, tiles;
   unit_counts(s, n_rows, n_kv_rows, per_req, units, tiles);
-  if (kv_pos) return units <= 1024 || (units <= 2048 && tiles >= 64);
+  if (kv_pos) {
+    if (s.d == 128 && units > 512 && tiles <= 8) return false;
+    return units <= 1024 || (units <= 2048 && tiles >= 64);
+  }
   return (double)units * (double)tiles * s.d <= 28672.0 * 128;
 }
 
