@@ -126,7 +126,8 @@ def _stream():
 
 class Prepared:
     """One validated, marshalled libqcf call.  Calling it enqueues the same launch
-    again -- on `stream` (a raw HIP stream handle) or torch's current stream --
+    again -- on `stream` (a raw HIP stream handle: an int, a c_void_p or anything that
+    ctypes takes for one, such as a torch stream) or torch's current stream --
     without repeating the argument checks and conversions; it keeps the tensors
     of the call alive.  Buffers must not be reallocated while it is in use.
 
@@ -138,12 +139,19 @@ class Prepared:
 
     def __init__(self, name, args, keep):
         types = EXPORTS[name][1]
+        if len(args) != len(types) - 1:
+            raise QcfError(f"{name} takes {len(types) - 1} arguments and a stream, got {len(args)}")
         self.name, self.keep = name, keep
         self.fn = getattr(_untyped(), name)
         self.args = tuple(a if isinstance(a, t) else t(a) for a, t in zip(args, types))
 
     def __call__(self, stream=None):
-        st = self.fn(*self.args, _stream() if stream is None else stream)
+        if stream is None:
+            stream = _stream()
+        elif type(stream) is not _P:
+            # without declared types ctypes would pass a Python int as a 32-bit C int
+            stream = _P.from_param(stream)
+        st = self.fn(*self.args, stream)
         if st:
             _check(st, self.name)
 

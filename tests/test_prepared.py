@@ -1,0 +1,55 @@
+"""Prepared calls hand every argument and the stream to the entry point whole (no GPU: the entry
+point is replaced by a recorder that is called through ctypes the same way)."""
+import ctypes
+import os
+
+import pytest
+import torch
+
+from paper_2606_05875_amd import qcf
+
+HANDLE = 0x7F1234567890          # an address as a runtime hands it out: more than 32 bits
+
+
+@pytest.fixture(scope="module", autouse=True)
+def built():
+    if not os.path.exists(qcf.lib_path()):
+        from paper_2606_05875_amd.build import build
+        build(verbose=False)
+
+
+def recorded(name, args):
+    """A Prepared call of `name` whose entry point records what arrives (an untyped function)."""
+    seen = []
+    types = qcf.EXPORTS[name][1]
+    callback = ctypes.CFUNCTYPE(ctypes.c_int, *types)(lambda *a: seen.append(a) or 0)
+    p = qcf.Prepared(name, args, callback)
+    p.fn = ctypes.CDLL(None)._FuncPtr(ctypes.cast(callback, ctypes.c_void_p).value)
+    return p, seen
+
+
+class Holder:                    # what torch.cuda.Stream offers ctypes
+    _as_parameter_ = ctypes.c_void_p(HANDLE)
+
+
+# the stream is passed in a register by the first entry point and on the stack by the second
+@pytest.mark.parametrize("name,args", [
+    ("qcf_rope_table", (ctypes.c_void_p(HANDLE + 16), ctypes.c_void_p(HANDLE + 32), 2 ** 31 - 1, 128, 1e6)),
+    ("qcf_gather_rows", (ctypes.c_void_p(HANDLE + 16), None, HANDLE + 48, 2 ** 40, 5, 64, 2 ** 33, 64)),
+])
+def test_arguments_and_stream_arrive_whole(name, args, monkeypatch):
+    monkeypatch.setattr(qcf, "_stream", lambda: ctypes.c_void_p(HANDLE + 8))
+    p, seen = recorded(name, args)
+    plain = lambda a: a.value if isinstance(a, ctypes.c_void_p) else a
+    for given, want in ((HANDLE, HANDLE), (ctypes.c_void_p(HANDLE), HANDLE), (Holder(), HANDLE),
+                        (None, HANDLE + 8), (0, None), (2 ** 63 + 5, 2 ** 63 + 5)):
+        p(given)
+        assert seen[-1][-1] == want, given
+        assert seen[-1][:-1] == tuple(plain(a) for a in args)
+
+
+def test_a_wrong_number_of_arguments_is_refused():
+    args = (ctypes.c_void_p(HANDLE), ctypes.c_void_p(HANDLE), 1, 128, 1e6)
+    for bad in (args[:-1], args + (0,)):
+        with pytest.raises(qcf.QcfError):
+            qcf.Prepared("qcf_rope_table", bad, None)
