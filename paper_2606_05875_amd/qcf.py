@@ -156,8 +156,13 @@ class Prepared:
             _check(st, self.name)
 
 
-class _Nothing:
+class _Nothing(Prepared):
     """A prepared call with nothing to launch."""
+
+    __slots__ = ()
+
+    def __init__(self, name):
+        self.name, self.fn, self.args, self.keep = name, lambda *a: 0, (), None
 
     def __call__(self, stream=None):
         pass
@@ -188,7 +193,7 @@ def prepare(call, *args, **kwargs) -> Prepared:
     finally:
         _REC.on, _REC.keep = False, None
     out, _REC.out = _REC.out, None
-    return out if out is not None else _Nothing()
+    return out if out is not None else _Nothing(getattr(call, "__name__", "noop"))
 
 
 def _dev(t, name, dtype=None):

@@ -4,7 +4,6 @@ import ctypes
 import os
 
 import pytest
-import torch
 
 from paper_2606_05875_amd import qcf
 
@@ -53,3 +52,10 @@ def test_a_wrong_number_of_arguments_is_refused():
     for bad in (args[:-1], args + (0,)):
         with pytest.raises(qcf.QcfError):
             qcf.Prepared("qcf_rope_table", bad, None)
+
+
+def test_a_call_with_nothing_to_launch_is_a_prepared_call():
+    p = qcf.prepare(lambda: None)
+    assert isinstance(p, qcf.Prepared)
+    assert p.name == "<lambda>" and p.args == () and p.keep is None and p.fn() == 0
+    assert p() is None and p(HANDLE) is None
