@@ -1108,11 +1108,21 @@ __global__ __launch_bounds__(kThreads) void attn_stream_merge_kernel(
   }
 }
 
-// Stream mode is used where 4-wave blocks, one per row tile, would be too few (use_w4) and the
-// row tiles fit the block's plan.  Its workspace: the plan (step prefix sums and key ends of
-// up to kMaxStreamTiles row tiles) and two partial slots per block.
-bool use_stream(const AttnShape& s, int max_tiles) {
-  return !use_w4(s) && (int64_t)max_tiles * s.batch <= kMaxStreamTiles && s.max_kv > kKT;
+// Stream mode is used where 4-wave blocks, one per row tile, would be too few (use_w4), the row
+// tiles fit the block's plan and the caller's bounds give fewer than 1.5 tiles of 256 query
+// vectors per CU.  The last condition is one of precision: the partials of cut tiles are rounded
+// to bf16, so calls whose tiles fill the chip are computed whole.  (Requests that fit one tile
+// of either size have as many of 128 as of 256 vectors, so use_w4's bound alone would cut 384 to
+// 511 of them.)  Its workspace: the plan (step prefix sums and key ends of up to kMaxStreamTiles
+// row tiles) and two partial slots per block.  `shape` as the caller gave it, `s` with its
+// max_rows bounded by the rows there are.
+bool use_stream(const AttnShape& shape, const AttnShape& s) {
+  int lg = 0;
+  while ((1 << lg) < s.hq / s.hkv) ++lg;
+  const int rpb = kW8Qv >> lg;
+  const int64_t tiles = ((int64_t)shape.max_rows + rpb - 1) / rpb * s.batch;
+  return !use_w4(s) && 2 * tiles * s.hkv < 3 * kStreamBlocks && tiles <= kMaxStreamTiles &&
+         s.max_kv > kKT;
 }
 
 struct StreamLayout {
@@ -1146,7 +1156,36 @@ int cu_count() {
   return n;
 }
 
+AttnShape bounded(const AttnShape& shape, int64_t n_rows) {
+  AttnShape s = shape;
+  s.max_rows = (int)std::min<int64_t>(s.max_rows, n_rows);  // no request has more rows than there are
+  return s;
+}
+
 }  // namespace
+
+AttnRoute attn_route(const AttnShape& shape, int64_t n_rows, int64_t n_kv_rows, bool bf16,
+                     bool kv_pos, bool ws) {
+  if (!bf16) return AttnRoute::kF32;
+  const AttnShape s = bounded(shape, n_rows);
+  if (use_keysplit(s, n_rows, n_kv_rows, kv_pos)) return AttnRoute::kKeySplit;
+  if (kv_pos) return AttnRoute::kPos;
+  if (use_stream(shape, s)) return AttnRoute::kStream;
+  // One request with at least four row tiles per CU: 8-wave blocks whose tiles come from work
+  // queues (counters in the workspace, reset by a kernel on the same stream); an eighth
+  // more blocks let the fast XCDs take tiles from the slow ones.  Measured on one box
+  // against the fixed order: 32 x 1024-token context (9.7 tiles per CU) -1.7 to -2.1%,
+  // 16 x 1024 (4.9) -1%, 8 x 1024 (2.4) +1.9%, ragged 16-request batch +1 to +2%.  Other
+  // calls take the 4-wave blocks in a fixed order.
+  int lg = 0;
+  while ((1 << lg) < s.hq / s.hkv) ++lg;
+  const int rpb = kW8Qv >> lg;
+  const int64_t nblocks = ((int64_t)s.max_rows + rpb - 1) / rpb * s.hkv;
+  if (ws && s.batch == 1 && nblocks >= 4 * (int64_t)cu_count() &&
+      nblocks + nblocks / 8 <= 0x7fffffff)
+    return AttnRoute::kQueue;
+  return AttnRoute::kW4;
+}
 
 size_t attn_workspace(const AttnShape& s, bool bf16) {
   // Every call that could choose stream mode needs the same layout (it only
@@ -1162,8 +1201,7 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
                               const AttnShape& shape, float scale, void* ws, hipStream_t stream,
                               const QueryRot& qrot) {
   if (n_rows == 0 || shape.batch == 0 || shape.max_rows == 0) return hipSuccess;
-  AttnShape s = shape;
-  s.max_rows = (int)std::min<int64_t>(s.max_rows, n_rows);  // no request has more rows than there are
+  const AttnShape s = bounded(shape, n_rows);
   const bool rot = qrot.table != nullptr;
   if (rot && (!bf16 || kv_pos)) return hipErrorInvalidValue;
   const float2* rtab = reinterpret_cast<const float2*>(qrot.table);
@@ -1173,14 +1211,18 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
   // recomputed rows: the buffer offsets of one request's rows are 32-bit
   if (bf16 && !kv_pos && (double)s.max_kv * (double)kv_row_stride * 2.0 >= 2147483648.0)
     return hipErrorInvalidConfiguration;
+  const AttnRoute route = attn_route(shape, n_rows, n_kv_rows, bf16, kv_pos != nullptr, ws != nullptr);
   // the workspace holds stream_layout's bytes whenever attn_workspace asks for one
-  if (bf16 && use_keysplit(s, n_rows, n_kv_rows, kv_pos != nullptr))
+  if (route == AttnRoute::kKeySplit)
     return launch_attn_keysplit(out, lse, q, row_pos, n_rows, cu_rows, k_cache, v_cache, n_kv_rows,
                                 kv_row_stride, cu_kv, kv_pos, s, scale, ws,
                                 ws ? attn_workspace(s, true) : 0, stream, qrot);
-  if (bf16 && !kv_pos) {
+  if (route == AttnRoute::kW4)
+    return launch_attn_w4(out, lse, q, row_pos, n_rows, cu_rows, k_cache, v_cache, n_kv_rows,
+                          kv_row_stride, cu_kv, s, scale, stream, qrot);
+  if (route == AttnRoute::kStream || route == AttnRoute::kQueue) {
     const int max_tiles = (s.max_rows + (kW8Qv >> lg) - 1) / (kW8Qv >> lg);
-    if (use_stream(s, max_tiles)) {
+    if (route == AttnRoute::kStream) {
       const StreamLayout L = stream_layout(s);
       char* wb = static_cast<char*>(ws);
       int32_t* plan = reinterpret_cast<int32_t*>(wb + L.plan_off);
@@ -1205,17 +1247,7 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
 #undef QCF_W8S
       return hipGetLastError();
     }
-    // One request with at least four row tiles per CU: 8-wave blocks whose tiles come from work
-    // queues (counters in the workspace, reset by a kernel on the same stream); an eighth
-    // more blocks let the fast XCDs take tiles from the slow ones.  Measured on one box
-    // against the fixed order: 32 x 1024-token context (9.7 tiles per CU) -1.7 to -2.1%,
-    // 16 x 1024 (4.9) -1%, 8 x 1024 (2.4) +1.9%, ragged 16-request batch +1 to +2%.  Other
-    // calls take the 4-wave blocks in a fixed order.
     const int64_t nblocks = (int64_t)max_tiles * s.hkv;
-    if (!ws || s.batch != 1 || nblocks < 4 * (int64_t)cu_count() ||
-        nblocks + nblocks / 8 > 0x7fffffff)
-      return launch_attn_w4(out, lse, q, row_pos, n_rows, cu_rows, k_cache, v_cache, n_kv_rows,
-                            kv_row_stride, cu_kv, s, scale, stream, qrot);
     const dim3 grid((unsigned)(nblocks + nblocks / 8));
     uint32_t* queue =
         reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + stream_layout(s).queue_off);
@@ -1234,7 +1266,7 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
 #undef QCF_W8
     return hipGetLastError();
   }
-  if (bf16) {
+  if (route == AttnRoute::kPos) {
     // explicit key positions (the anchor probe): the 4-wave kernel
     const int max_tiles = (s.max_rows + (128 >> lg) - 1) / (128 >> lg);
     const int64_t nblocks = (int64_t)max_tiles * s.batch * s.hkv;

@@ -127,6 +127,12 @@ struct QueryRot {
   int64_t n_table;
 };
 size_t attn_workspace(const AttnShape& s, bool bf16);
+// Which kernel takes an attention call (the tests ask too): float32; blocks whose waves split
+// the keys; the persistent grid; tiles from work queues; 4-wave blocks, one per row tile; large
+// probes with explicit key positions.
+enum class AttnRoute : int { kF32, kKeySplit, kStream, kQueue, kW4, kPos };
+AttnRoute attn_route(const AttnShape& s, int64_t n_rows, int64_t n_kv_rows, bool bf16, bool kv_pos,
+                     bool ws);
 hipError_t launch_attn_f32(float* out, float* lse, const float* q, const int32_t* row_pos,
                            int64_t n_rows, const int32_t* cu_rows, const float* k_cache,
                            const float* v_cache, int64_t n_kv_rows, int64_t kv_row_stride,

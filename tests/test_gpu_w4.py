@@ -10,6 +10,7 @@ import torch
 from oracle import qcfuse as Q
 from paper_2606_05875_amd import qcf
 from parity import assert_close
+from routes import batch_route
 from test_gpu_kernels import dev, draw, host, padded, say
 
 pytestmark = pytest.mark.gpu
@@ -58,3 +59,23 @@ def test_attention_w4(hq, hkv, d, n_kv, n_rows, pad, rot):
         r, h = pick[-1], hq - 1
         lg = (k[ka:ka + pos[r] + 1, hkv - 1].astype(np.float64) @ q[r, h].astype(np.float64)) / math.sqrt(d)
         assert abs(float(lse[r, h]) - np.log(np.exp(lg - lg.max()).sum()) - lg.max()) < 2e-3
+
+
+def test_requests_of_one_tile_are_computed_whole():
+    """48 requests of one row tile each: every tile is computed whole, so a request's rows have the
+    same bits as in a batch of 64 (which fills the 4-wave grid)."""
+    hq, hkv, d, n_kv, rows = 32, 8, 128, 1600, 32
+    say("attention, one tile per request", n_kv, rows)
+    gen = torch.Generator(device="cuda").manual_seed(52)
+    new = lambda n, h: torch.randn((n, h, d), generator=gen, device="cuda").to(torch.bfloat16)
+    k, v, q = new(64 * n_kv, hkv), new(64 * n_kv, hkv), new(64 * rows, hq)
+    pos = torch.arange(n_kv - rows, n_kv, dtype=torch.int32, device="cuda").repeat(64)
+    outs = []
+    for reqs in (48, 64):
+        assert batch_route([rows] * reqs, [n_kv] * reqs, hq, hkv, d) == "w4"
+        cu = lambda n: dev(np.arange(reqs + 1, dtype=np.int32) * n)
+        out = torch.empty((reqs * rows, hq, d), dtype=torch.bfloat16, device="cuda")
+        qcf.qcf_sparse_prefill_attn(out, q[:reqs * rows], pos[:reqs * rows], cu(rows), k[:reqs * n_kv],
+                                    v[:reqs * n_kv], cu(n_kv), rows, n_kv, 1 / math.sqrt(d))
+        outs.append(out)
+    assert torch.equal(outs[0], outs[1][:48 * rows])
