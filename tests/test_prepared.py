@@ -2,6 +2,7 @@
 point is replaced by a recorder that is called through ctypes the same way)."""
 import ctypes
 import os
+from types import SimpleNamespace
 
 import pytest
 
@@ -17,14 +18,17 @@ def built():
         build(verbose=False)
 
 
-def recorded(name, args):
-    """A Prepared call of `name` whose entry point records what arrives (an untyped function)."""
+def recorded(name, args, monkeypatch):
+    """A Prepared call of `name` whose entry point, on both handles, records what arrives."""
     seen = []
     types = qcf.EXPORTS[name][1]
     callback = ctypes.CFUNCTYPE(ctypes.c_int, *types)(lambda *a: seen.append(a) or 0)
-    p = qcf.Prepared(name, args, callback)
-    p.fn = ctypes.CDLL(None)._FuncPtr(ctypes.cast(callback, ctypes.c_void_p).value)
-    return p, seen
+    address = ctypes.cast(callback, ctypes.c_void_p).value
+    typed, untyped = ctypes.CDLL(None)._FuncPtr(address), ctypes.CDLL(None)._FuncPtr(address)
+    typed.restype, typed.argtypes = qcf.EXPORTS[name]
+    monkeypatch.setattr(qcf, "lib", lambda: SimpleNamespace(**{name: typed}))
+    monkeypatch.setattr(qcf, "_untyped", lambda: SimpleNamespace(**{name: untyped}))
+    return qcf.Prepared(name, args, callback), seen
 
 
 class Holder:                    # what torch.cuda.Stream offers ctypes
@@ -38,10 +42,11 @@ class Holder:                    # what torch.cuda.Stream offers ctypes
 ])
 def test_arguments_and_stream_arrive_whole(name, args, monkeypatch):
     monkeypatch.setattr(qcf, "_stream", lambda: ctypes.c_void_p(HANDLE + 8))
-    p, seen = recorded(name, args)
+    p, seen = recorded(name, args, monkeypatch)
     plain = lambda a: a.value if isinstance(a, ctypes.c_void_p) else a
-    for given, want in ((HANDLE, HANDLE), (ctypes.c_void_p(HANDLE), HANDLE), (Holder(), HANDLE),
-                        (None, HANDLE + 8), (0, None), (2 ** 63 + 5, 2 ** 63 + 5)):
+    # the first call takes the declared entry point, the others the one without declared types
+    for given, want in ((HANDLE, HANDLE), (HANDLE, HANDLE), (ctypes.c_void_p(HANDLE), HANDLE),
+                        (Holder(), HANDLE), (None, HANDLE + 8), (0, None), (2 ** 63 + 5, 2 ** 63 + 5)):
         p(given)
         assert seen[-1][-1] == want, given
         assert seen[-1][:-1] == tuple(plain(a) for a in args)
@@ -59,3 +64,17 @@ def test_a_call_with_nothing_to_launch_is_a_prepared_call():
     assert isinstance(p, qcf.Prepared)
     assert p.name == "<lambda>" and p.args == () and p.keep is None and p.fn() == 0
     assert p() is None and p(HANDLE) is None
+
+
+def test_a_call_made_once_converts_nothing(monkeypatch):
+    """A new step prepares and calls each of its calls once: its first pass must not pay for the
+    conversion that makes the later ones cheap."""
+    monkeypatch.setattr(qcf, "_stream", lambda: ctypes.c_void_p(HANDLE))
+    args = (ctypes.c_void_p(HANDLE + 16), ctypes.c_void_p(HANDLE + 32), 5, 128, 1e6)
+    p, seen = recorded("qcf_rope_table", args, monkeypatch)
+    p()
+    assert p.args is args
+    p()
+    assert isinstance(p.args[2], ctypes.c_int64) and isinstance(p.args[4], ctypes.c_double)
+    p()
+    assert seen[0] == seen[1] == seen[2] and len(seen) == 3
