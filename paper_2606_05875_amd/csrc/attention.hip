@@ -21,8 +21,9 @@
 // Recomputed rows: one long request on attn_w8_kernel (8 waves, 256 query vectors, a
 // 4-stage K/V ring filled by buffer loads; the products run as fenced sequences with
 // their LDS fragment reads issued four products ahead; the two waves of a SIMD run the
-// step a product phase apart, and the row tiles come from per-XCD work queues); few,
-// unequal row tiles on its persistent "stream" grid; all others on 4-wave blocks
+// step a product phase apart, and the row tiles come from per-XCD work queues), and so
+// batches whose rows sit in few of their requests, one block per tile; few, unequal row
+// tiles on its persistent "stream" grid; all others on 4-wave blocks
 // (attention_w4.hip).  Large probes run on attn_pos_kernel (4 waves, K/V by global->LDS
 // loads two and one tiles ahead, key positions from a table).
 // Calls with few query vectors take attention_keysplit.hip.
@@ -764,61 +765,81 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
   };
 
   if (!kStream) {
-    // One long request: the items (row tile, KV head), last row tile (most keys) first, are
-    // handed out by counters in the workspace; the tile's whole key range (up to its
-    // largest row position) is this block's.  Queue j holds the tiles of KV heads j,
-    // j + nq, ...; a block takes from the queue of its XCD (whose L2 then serves one
-    // head's keys to all of its CUs) and, once that one is empty, from another that
-    // still has items.  Under load the XCDs run at different clocks, so the fast ones
-    // take over tiles that a fixed share per XCD would leave to the slow ones at the
-    // end.  The grid holds spare blocks for that; a block that finds every queue empty
-    // ends at once.
-    int tile;
-    const int nq = hkv < kQueues ? hkv : kQueues;
-    const int home = (int)((__builtin_amdgcn_s_getreg(kHwRegXccId) & 15u) % (uint32_t)nq);
-    uint32_t first_claim = 0;  // goes out before the request's row count is read
-    if (threadIdx.x == 0) first_claim = atomicAdd(queue + kQueueStride * home, 1u);
-    const int ntl = min(max_tiles, (max(cu_rows[1] - cu_rows[0], 0) + rpb - 1) / rpb);
-    auto items_of = [&](int j) { return ntl * ((hkv - j + nq - 1) / nq); };
-    // q_next is written only after a barrier that follows every wave's last read of
-    // it; everything derived from it is wave-uniform (scalar registers)
-    auto claim = [&](int j) {
+    // this block's row tile, all of its keys (up to its largest row position)
+    int tile, b = 0;
+    if (queue) {
+      // One long request: the items (row tile, KV head), last row tile (most keys) first, are
+      // handed out by counters in the workspace.  Queue j holds the tiles of KV heads j,
+      // j + nq, ...; a block takes from the queue of its XCD (whose L2 then serves one
+      // head's keys to all of its CUs) and, once that one is empty, from another that
+      // still has items.  Under load the XCDs run at different clocks, so the fast ones
+      // take over tiles that a fixed share per XCD would leave to the slow ones at the
+      // end.  The grid holds spare blocks for that; a block that finds every queue empty
+      // ends at once.
+      const int nq = hkv < kQueues ? hkv : kQueues;
+      const int home = (int)((__builtin_amdgcn_s_getreg(kHwRegXccId) & 15u) % (uint32_t)nq);
+      uint32_t first_claim = 0;  // goes out before the request's row count is read
+      if (threadIdx.x == 0) first_claim = atomicAdd(queue + kQueueStride * home, 1u);
+      const int ntl = min(max_tiles, (max(cu_rows[1] - cu_rows[0], 0) + rpb - 1) / rpb);
+      auto items_of = [&](int j) { return ntl * ((hkv - j + nq - 1) / nq); };
+      // q_next is written only after a barrier that follows every wave's last read of
+      // it; everything derived from it is wave-uniform (scalar registers)
+      auto claim = [&](int j) {
+        __syncthreads();
+        if (threadIdx.x == 0) q_next = (int)atomicAdd(queue + kQueueStride * j, 1u);
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(q_next);
+      };
+      auto next_queue = [&](int from) {  // the first queue after `from` with items left, or -1
+        __syncthreads();
+        if (w == 0) {
+          const int c = l < nq ? (int)__hip_atomic_load(queue + kQueueStride * l, __ATOMIC_RELAXED,
+                                                         __HIP_MEMORY_SCOPE_AGENT)
+                               : 0;
+          const bool left = l < nq && c < items_of(l);
+          const int dist = wave_min_i(left ? (l - from - 1 + 2 * nq) % nq : INT_MAX);
+          if (l == 0) q_next = dist == INT_MAX ? -1 : (from + 1 + dist) % nq;
+        }
+        __syncthreads();
+        return __builtin_amdgcn_readfirstlane(q_next);
+      };
+      int qj = home;
+      if (threadIdx.x == 0) q_next = (int)first_claim;
       __syncthreads();
-      if (threadIdx.x == 0) q_next = (int)atomicAdd(queue + kQueueStride * j, 1u);
-      __syncthreads();
-      return __builtin_amdgcn_readfirstlane(q_next);
-    };
-    auto next_queue = [&](int from) {  // the first queue after `from` with items left, or -1
-      __syncthreads();
-      if (w == 0) {
-        const int c = l < nq ? (int)__hip_atomic_load(queue + kQueueStride * l, __ATOMIC_RELAXED,
-                                                       __HIP_MEMORY_SCOPE_AGENT)
-                             : 0;
-        const bool left = l < nq && c < items_of(l);
-        const int dist = wave_min_i(left ? (l - from - 1 + 2 * nq) % nq : INT_MAX);
-        if (l == 0) q_next = dist == INT_MAX ? -1 : (from + 1 + dist) % nq;
+      int item = __builtin_amdgcn_readfirstlane(q_next);
+      while (item >= items_of(qj)) {  // (each failed claim finds a queue empty for good)
+        qj = next_queue(home);
+        if (qj < 0) return;
+        item = claim(qj);
       }
-      __syncthreads();
-      return __builtin_amdgcn_readfirstlane(q_next);
-    };
-    int qj = home;
-    if (threadIdx.x == 0) q_next = (int)first_claim;
-    __syncthreads();
-    int item = __builtin_amdgcn_readfirstlane(q_next);
-    while (item >= items_of(qj)) {  // (each failed claim finds a queue empty for good)
-      qj = next_queue(home);
-      if (qj < 0) return;
-      item = claim(qj);
+      const int hj = items_of(qj) / ntl;  // KV heads of queue qj
+      const int u = item / hj;
+      tile = ntl - 1 - u;
+      g = qj + nq * (item - u * hj);
+    } else {
+      // A batch whose rows sit in few of its requests: the blocks of one KV head run the requests
+      // one after another, longest (most keys) first, each request's tiles last row tile first.
+      const int rest = blockIdx.x / hkv;
+      const int rank = rest / max_tiles;
+      tile = max_tiles - 1 - (rest - rank * max_tiles);
+      b = rank;
+      if (batch > 1 && batch <= 64) {
+        // rank of lane j's request: requests with more keys, or as many and a lower index
+        const int nk = l < batch ? cu_kv[l + 1] - cu_kv[l] : -1;
+        int rk = 0;
+        for (int x = 0; x < batch; ++x) {
+          const int nx = __shfl(nk, x, 64);
+          rk += (nx > nk || (nx == nk && x < l)) ? 1 : 0;
+        }
+        const uint64_t hit = __ballot(l < batch && rk == rank);
+        b = __builtin_amdgcn_readfirstlane(hit ? (int)__builtin_ctzll(hit) : rank);
+      }
     }
-    const int hj = items_of(qj) / ntl;  // KV heads of queue qj
-    const int u = item / hj;
-    tile = ntl - 1 - u;
-    g = qj + nq * (item - u * hj);
-    const int64_t r0 = cu_rows[0];
-    const int nr = cu_rows[1] - (int)r0;
+    const int64_t r0 = cu_rows[b];
+    const int nr = cu_rows[b + 1] - (int)r0;
     if (tile * rpb >= nr) return;
-    const int64_t kv0 = cu_kv[0];
-    int nkv = cu_kv[1] - (int)kv0;
+    const int64_t kv0 = cu_kv[b];
+    int nkv = cu_kv[b + 1] - (int)kv0;
     if (kv0 + nkv > n_kv_rows) nkv = (int)(n_kv_rows - kv0);
     const int rl = tile * rpb + (qv >> lg);
     const int pos_raw = row_pos[min(r0 + rl, n_rows - 1)];
@@ -1108,23 +1129,6 @@ __global__ __launch_bounds__(kThreads) void attn_stream_merge_kernel(
   }
 }
 
-// Stream mode is used where 4-wave blocks, one per row tile, would be too few (use_w4), the row
-// tiles fit the block's plan and the caller's bounds give fewer than 1.5 tiles of 256 query
-// vectors per CU.  The last condition is one of precision: the partials of cut tiles are rounded
-// to bf16, so calls whose tiles fill the chip are computed whole.  (Requests that fit one tile
-// of either size have as many of 128 as of 256 vectors, so use_w4's bound alone would cut 384 to
-// 511 of them.)  Its workspace: the plan (step prefix sums and key ends of up to kMaxStreamTiles
-// row tiles) and two partial slots per block.  `shape` as the caller gave it, `s` with its
-// max_rows bounded by the rows there are.
-bool use_stream(const AttnShape& shape, const AttnShape& s) {
-  int lg = 0;
-  while ((1 << lg) < s.hq / s.hkv) ++lg;
-  const int rpb = kW8Qv >> lg;
-  const int64_t tiles = ((int64_t)shape.max_rows + rpb - 1) / rpb * s.batch;
-  return !use_w4(s) && 2 * tiles * s.hkv < 3 * kStreamBlocks && tiles <= kMaxStreamTiles &&
-         s.max_kv > kKT;
-}
-
 struct StreamLayout {
   int nbg;
   size_t plan_off, o_off, ml_off, queue_off, bytes;
@@ -1164,27 +1168,58 @@ AttnShape bounded(const AttnShape& shape, int64_t n_rows) {
 
 }  // namespace
 
+// Row tiles of qv query vectors (rows times the heads of one KV head) in a call: `padded` if every
+// request had max_rows rows, `most` that n_rows rows can make.
+static void tile_counts(const AttnShape& s, int64_t n_rows, int qv, int64_t& padded, int64_t& most) {
+  int lg = 0;
+  while ((1 << lg) < s.hq / s.hkv) ++lg;
+  const int rpb = qv >> lg;
+  padded = ((int64_t)s.max_rows + rpb - 1) / rpb * s.batch * s.hkv;
+  most = std::min(padded, (std::max<int64_t>(n_rows - s.batch, 0) / rpb + s.batch) * s.hkv);
+}
+
+// Recomputed rows too many for the key-split kernel.  Whole layer calls, us, 32/8 heads; "few"
+// names batches whose rows sit in few of their requests (padded > 1.5 most).
+//  * The persistent grid rounds the partials of cut tiles to bf16, so it takes a call only if the
+//    caller's bounds give fewer than 1.5 tiles of 256 vectors per CU (and the tiles fit its plan):
+//    tiles that fill the chip are computed whole.  (Requests that fit one tile of either size
+//    have as many of 128 as of 256: 48 of 32 rows, 2500 keys 110 us whole, 130 cut.)
+//  * Of those it evens out few and unequal tiles but pays for its plan and the merge.  4-wave
+//    blocks against it, head size 128: at most 512 tiles of 128 (two per CU) 96 / 95 us (2 x 1000
+//    rows, 4096 keys), 608 of them 53 / 77; fewer tiles lose over long ranges (few, at most 272:
+//    97 / 64; 200 of 2048 keys 52 / 44; one request's 400 of up to 81 key steps 119 / 113) and
+//    win over up to 24 key steps (192 tiles 31 / 39, 320 33 / 46; few, at most 88: 29 / 34), but for
+//    few tiles of few requests at head size 64 (192: 31.3 / 27.9; at 128 38.7 / 38.6).
+//  * One request with at least four tiles of 256 per CU: 8-wave blocks whose tiles come from work
+//    queues (counters in the workspace, reset by a kernel on the same stream); an eighth more
+//    blocks let the fast XCDs take tiles from the slow ones.  Against the fixed order: 32 x
+//    1024-token context (9.7 tiles per CU) -1.7 to -2.1%, 16 x 1024 (4.9) -1%, 8 x 1024 (2.4)
+//    +1.9%, ragged 16-request batch +1 to +2%.
+//  * Other whole tiles: 4-wave blocks, two per CU, hide each other's ends (20 x 512-token layer
+//    291 / 283, 16-request batch 1835 / 1801 with 8-wave / 4-wave blocks); but a tile that is alone
+//    on its CU waits for its keys in every step, where the 8-wave block's ring is deeper.  So few
+//    requests whose tiles of 256 all fit the chip at once (and one more per KV head) take 8-wave
+//    blocks: 900 + 3 x 20 rows, 3000 keys 73 / 82, 8192 keys 179 / 207; 2 x 600 + 4 x 10 rows, 3000
+//    keys 72 / 84; 2000 + 16 rows, 8000 keys 214 / 232; beyond that 3 x 600 + 4 x 10 rows 100 / 94.
 AttnRoute attn_route(const AttnShape& shape, int64_t n_rows, int64_t n_kv_rows, bool bf16,
                      bool kv_pos, bool ws) {
   if (!bf16) return AttnRoute::kF32;
   const AttnShape s = bounded(shape, n_rows);
   if (use_keysplit(s, n_rows, n_kv_rows, kv_pos)) return AttnRoute::kKeySplit;
   if (kv_pos) return AttnRoute::kPos;
-  if (use_stream(shape, s)) return AttnRoute::kStream;
-  // One request with at least four row tiles per CU: 8-wave blocks whose tiles come from work
-  // queues (counters in the workspace, reset by a kernel on the same stream); an eighth
-  // more blocks let the fast XCDs take tiles from the slow ones.  Measured on one box
-  // against the fixed order: 32 x 1024-token context (9.7 tiles per CU) -1.7 to -2.1%,
-  // 16 x 1024 (4.9) -1%, 8 x 1024 (2.4) +1.9%, ragged 16-request batch +1 to +2%.  Other
-  // calls take the 4-wave blocks in a fixed order.
-  int lg = 0;
-  while ((1 << lg) < s.hq / s.hkv) ++lg;
-  const int rpb = kW8Qv >> lg;
-  const int64_t nblocks = ((int64_t)s.max_rows + rpb - 1) / rpb * s.hkv;
-  if (ws && s.batch == 1 && nblocks >= 4 * (int64_t)cu_count() &&
-      nblocks + nblocks / 8 <= 0x7fffffff)
+  int64_t padded, most, pad256, most256, caller256, unused;
+  tile_counts(s, n_rows, 128, padded, most);
+  tile_counts(s, n_rows, kW8Qv, pad256, most256);
+  tile_counts(shape, n_rows, kW8Qv, caller256, unused);
+  const bool few = 2 * padded > 3 * most;
+  if (2 * caller256 < 3 * kStreamBlocks && caller256 / s.hkv <= kMaxStreamTiles && s.max_kv > kKT) {
+    const bool w4 = most >= 2 * kStreamBlocks || (s.max_kv <= 24 * kKT && !(s.d == 64 && few && most < kStreamBlocks));
+    return w4 ? AttnRoute::kW4 : AttnRoute::kStream;
+  }
+  const int64_t cus = cu_count();
+  if (ws && s.batch == 1 && pad256 >= 4 * cus && pad256 + pad256 / 8 <= 0x7fffffff)
     return AttnRoute::kQueue;
-  return AttnRoute::kW4;
+  return few && most256 <= cus + s.hkv ? AttnRoute::kPlain : AttnRoute::kW4;
 }
 
 size_t attn_workspace(const AttnShape& s, bool bf16) {
@@ -1220,7 +1255,7 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
   if (route == AttnRoute::kW4)
     return launch_attn_w4(out, lse, q, row_pos, n_rows, cu_rows, k_cache, v_cache, n_kv_rows,
                           kv_row_stride, cu_kv, s, scale, stream, qrot);
-  if (route == AttnRoute::kStream || route == AttnRoute::kQueue) {
+  if (route == AttnRoute::kStream || route == AttnRoute::kQueue || route == AttnRoute::kPlain) {
     const int max_tiles = (s.max_rows + (kW8Qv >> lg) - 1) / (kW8Qv >> lg);
     if (route == AttnRoute::kStream) {
       const StreamLayout L = stream_layout(s);
@@ -1247,11 +1282,15 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
 #undef QCF_W8S
       return hipGetLastError();
     }
-    const int64_t nblocks = (int64_t)max_tiles * s.hkv;
-    const dim3 grid((unsigned)(nblocks + nblocks / 8));
-    uint32_t* queue =
-        reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + stream_layout(s).queue_off);
-    attn_queue_reset_kernel<<<1, 64, 0, stream>>>(queue);
+    int64_t nblocks = (int64_t)max_tiles * s.batch * s.hkv;
+    uint32_t* queue = nullptr;
+    if (route == AttnRoute::kQueue) {
+      queue = reinterpret_cast<uint32_t*>(static_cast<char*>(ws) + stream_layout(s).queue_off);
+      attn_queue_reset_kernel<<<1, 64, 0, stream>>>(queue);
+      nblocks += nblocks / 8;
+    }
+    if (nblocks > 0x7fffffff) return hipErrorInvalidConfiguration;
+    const dim3 grid((unsigned)nblocks);
 #define QCF_W8(D, R)                                                                              \
   attn_w8_kernel<D, false, R><<<grid, kW8 * 64, 0, stream>>>(                                     \
       static_cast<uint16_t*>(out), lse, static_cast<const uint16_t*>(q), row_pos, n_rows, cu_rows, \

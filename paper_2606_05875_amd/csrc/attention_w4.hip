@@ -340,33 +340,16 @@ __global__ __launch_bounds__(kW * 64, 2) void attn_w4_kernel(
 
 }  // namespace
 
-// Row tiles of a call: 128 query vectors of one request and KV head each (at most max_rows rows).
-static int64_t tile_count(const AttnShape& s, int lg, int& max_tiles) {
-  const int rpb = kQv >> lg;
-  max_tiles = (s.max_rows + rpb - 1) / rpb;
-  return (int64_t)max_tiles * s.batch * s.hkv;
-}
-
-// Against the persistent grid of 8-wave blocks, which evens out few and unequal tiles but pays
-// for its plan and the merge (whole layer recompute, us, this kernel / the persistent grid): 640
-// tiles of up to 129 key steps 206 / 214, 672 of up to 41 81 / 105, ~544 in four requests 47 /
-// 56; 136 of up to 25 steps 43.5 / 46.0; 400 of up to 81 119 / 113, 208 of up to 41 65.5 / 56.6,
-// 400 of up to 81 at head size 64 96 / 77.  So: a tile for every block that the chip holds
-// (two per CU), or short key ranges.
-bool use_w4(const AttnShape& s) {
-  int lg = 0, max_tiles;
-  while ((1 << lg) < s.hq / s.hkv) ++lg;
-  return tile_count(s, lg, max_tiles) >= 512 || s.max_kv <= 24 * kKT;
-}
-
 hipError_t launch_attn_w4(void* out, float* lse, const void* q, const int32_t* row_pos,
                           int64_t n_rows, const int32_t* cu_rows, const void* k_cache,
                           const void* v_cache, int64_t n_kv_rows, int64_t kv_row_stride,
                           const int32_t* cu_kv, const AttnShape& s, float scale,
                           hipStream_t stream, const QueryRot& qrot) {
-  int lg = 0, max_tiles;
+  int lg = 0;
   while ((1 << lg) < s.hq / s.hkv) ++lg;
-  const int64_t blocks = tile_count(s, lg, max_tiles);
+  const int rpb = kQv >> lg;
+  const int max_tiles = (s.max_rows + rpb - 1) / rpb;  // row tiles of the longest request
+  const int64_t blocks = (int64_t)max_tiles * s.batch * s.hkv;
   if (blocks > 0x7fffffff) return hipErrorInvalidConfiguration;
   const float2* rtab = reinterpret_cast<const float2*>(qrot.table);
 #define QCF_W4(D, R)                                                                               \

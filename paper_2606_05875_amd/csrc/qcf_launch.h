@@ -129,8 +129,8 @@ struct QueryRot {
 size_t attn_workspace(const AttnShape& s, bool bf16);
 // Which kernel takes an attention call (the tests ask too): float32; blocks whose waves split
 // the keys; the persistent grid; tiles from work queues; 4-wave blocks, one per row tile; large
-// probes with explicit key positions.
-enum class AttnRoute : int { kF32, kKeySplit, kStream, kQueue, kW4, kPos };
+// probes with explicit key positions; 8-wave blocks, one per row tile.
+enum class AttnRoute : int { kF32, kKeySplit, kStream, kQueue, kW4, kPos, kPlain };
 AttnRoute attn_route(const AttnShape& s, int64_t n_rows, int64_t n_kv_rows, bool bf16, bool kv_pos,
                      bool ws);
 hipError_t launch_attn_f32(float* out, float* lse, const float* q, const int32_t* row_pos,
@@ -147,7 +147,6 @@ hipError_t launch_attn_keysplit(void* out, float* lse, const void* q, const int3
                                 float scale, void* ws, size_t ws_bytes, hipStream_t stream,
                                 const QueryRot& qrot);
 // bf16 recomputed rows on 4-wave blocks, one per row tile
-bool use_w4(const AttnShape& s);
 hipError_t launch_attn_w4(void* out, float* lse, const void* q, const int32_t* row_pos,
                           int64_t n_rows, const int32_t* cu_rows, const void* k_cache,
                           const void* v_cache, int64_t n_kv_rows, int64_t kv_row_stride,

@@ -4,7 +4,7 @@ import ctypes
 
 from paper_2606_05875_amd import qcf
 
-NAMES = ("f32", "keysplit", "stream", "queue", "w4", "pos")
+NAMES = ("f32", "keysplit", "stream", "queue", "w4", "pos", "plain")
 
 
 class _Shape(ctypes.Structure):

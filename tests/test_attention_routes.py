@@ -26,5 +26,28 @@ def test_tiles_that_fill_the_chip_are_not_cut():
     # a loose bound of the rows per request had given the whole-tile grid, and does
     args = dict(batch=4, max_kv=4096, hq=32, hkv=8, d=128, n_rows=450, n_kv_rows=4 * 4096)
     assert attn_route(max_rows=450, **args) == "stream"
-    assert attn_route(max_rows=800, **args) == "w4"
-    assert attn_route(max_rows=2 ** 31 - 1, **args) == "w4"
+    assert attn_route(max_rows=800, **args) == "plain"
+    assert attn_route(max_rows=2 ** 31 - 1, **args) == "plain"
+    args = dict(batch=1, max_kv=8192, hq=32, hkv=8, d=128, n_rows=1200, n_kv_rows=8192)
+    assert attn_route(max_rows=1200, **args) == "stream"
+    assert attn_route(max_rows=4000, **args) == "w4"
+
+
+def test_tiles_are_counted_by_the_rows_there_are():
+    """A batch whose rows sit in few of its requests has far fewer row tiles than its longest request
+    would give: padding is no reason to leave the persistent grid or the 8-wave blocks."""
+    route = lambda rows, kv, d=128: batch_route(rows, [kv] * len(rows), 32, 8, d)
+    for d in (64, 128):
+        assert route([1000, 32], 4096, d) == "stream"              # 512 tiles of 128 padded, 272 at most
+        assert route([700, 10, 10], 2048, d) == "stream"
+        assert route([1000, 1000], 4096, d) == "w4"                # 512 of them real
+        assert route([600] * 4, 2000, d) == "w4"
+        assert route([900, 20, 20, 20], 1500, d) == "plain"        # whole tiles, few of them
+        assert route([900, 20, 20, 20], 8192, d) == "plain"
+        assert route([2000, 16], 8000, d) == "plain"
+        assert route([600] * 3 + [10] * 4, 3000, d) == "w4"        # more tiles than fit the chip at once
+        assert route([3000, 30, 30, 30], 4000, d) == "w4"
+        assert route([1000] * 3 + [40], 6000, d) == "w4"
+        assert route([1250], 1536, d) == "w4"                      # short ranges
+        assert route([700, 10], 1400, d) == ("stream" if d == 64 else "w4")
+        assert route([1400, 10], 1536, d) == "w4"

@@ -79,3 +79,40 @@ def test_requests_of_one_tile_are_computed_whole():
                                     v[:reqs * n_kv], cu(n_kv), rows, n_kv, 1 / math.sqrt(d))
         outs.append(out)
     assert torch.equal(outs[0], outs[1][:48 * rows])
+
+
+@pytest.mark.parametrize("hq,hkv,d,n_kv,n_rows,rot", [
+    (32, 8, 128, [1500, 1100, 64, 1300], [900, 20, 0, 21], True),
+    (16, 2, 64, [700] + [300] * 31, [180] + [1] * 31, False),      # group 8
+    (8, 8, 64, [1400] + [65, 700, 64, 3] * 2, [1300] + [3] * 8, True),   # group 1
+])
+def test_few_requests_hold_the_rows(hq, hkv, d, n_kv, n_rows, rot):
+    """A batch whose rows sit in few of its requests runs on 8-wave blocks, one per row tile: every
+    16th row and the last one of every request against the oracle."""
+    say("attention, few requests hold the rows", hq, hkv, d, n_kv[:4], n_rows[:4], rot)
+    assert batch_route(n_rows, n_kv, hq, hkv, d) == "plain"
+    rng = np.random.default_rng(53)
+    cu = lambda x: np.concatenate([[0], np.cumsum(x)]).astype(np.int32)
+    cu_kv, cu_r = cu(n_kv), cu(n_rows)
+    k = draw(rng, (cu_kv[-1], hkv, d), "bf16", 1 / math.sqrt(d))
+    v = draw(rng, (cu_kv[-1], hkv, d), "bf16", 1 / math.sqrt(d))
+    q = draw(rng, (cu_r[-1], hq, d), "bf16", math.sqrt(d))
+    pos = np.concatenate([np.sort(rng.choice(n, m, replace=False)) for n, m in zip(n_kv, n_rows)]).astype(np.int32)
+    out = torch.full((cu_r[-1], hq, d), float("nan"), dtype=torch.bfloat16, device="cuda")
+    geo = (dev(q, torch.bfloat16), dev(pos), dev(cu_r), dev(k, torch.bfloat16), dev(v, torch.bfloat16), dev(cu_kv),
+           max(n_rows), max(n_kv), 1 / math.sqrt(d))
+    if rot:
+        qcf.qcf_sparse_prefill_attn_rope(out, *geo, qcf.rope_position_table(max(n_kv), d, 1e6))
+        q = Q.round_storage(Q.rope(q, pos, 1e6), "bf16")
+    else:
+        qcf.qcf_sparse_prefill_attn(out, *geo)
+    got = host(out)
+    assert np.isfinite(got).all()
+    for b in range(len(n_kv)):
+        a, e, ka, ke = cu_r[b], cu_r[b + 1], cu_kv[b], cu_kv[b + 1]
+        if e == a:
+            continue
+        pick = np.unique(np.concatenate([np.arange(a, e, 16), [e - 1]]))
+        want = Q.round_storage(Q.attention(q[pick], pos[pick], k[ka:ke], v[ka:ke], np.arange(ke - ka),
+                                           1 / math.sqrt(d), hkv), "bf16")
+        assert_close(got[pick], want, "bf16", f"request {b}")
