@@ -320,8 +320,12 @@ static void unit_counts(const AttnShape& s, int64_t n_rows, int64_t n_kv_rows, i
 // Where splitting the keys over waves beats sharing tiles between them (whole calls, us, this
 // kernel against the shared-tile one).
 //  * Explicit key positions: 64 units x 35 tiles 14.5 / 65.6; 64 x 322 30 / 548; 256 x 36
-//    16.1 / 66.6; 256 x 1028 228 / 1748; 2048 x 130 110 / 172; 2048 x 9 31.7 / 31.3;
-//    4096 x 9 82 / 57; 4096 x 66 315 / 276.  Short ranges at head size 128, where blocks that
+//    16.1 / 66.6; 256 x 1028 228 / 1748; 1024 x 9 23.3 / 23.7, x 50 67 / 93; 2048 x 9 31.7 /
+//    31.3; 4096 x 9 82 / 57; 4096 x 66 315 / 276.  Beyond 1024 units over long ranges the
+//    shared-tile kernel's blocks come to fill the chip too (2048 units: one round of two per
+//    CU): head size 128, 1536 x 66 120 / 137, 1792 x 66 138 / 137, x 100 191 / 203, x 200 368 /
+//    408, 1920 x 66 156 / 138, 2048 x 66 161 / 138, x 100 214 / 203; head size 64, 2048 x 66
+//    101 / 114, x 200 255 / 331.  Short ranges at head size 128, where blocks that
 //    no longer fit the chip at once start for little work: 512 x 3 11.8 / 12.3, 720 x 6 17.7 /
 //    16.7, 720 x 8 20.1 / 19.8, 1024 x 3 15.5 / 13.5, 720 x 12 24.9 / 26.5 (head size 64, smaller
 //    blocks: 1024 x 3 7.7 / 10.3).
@@ -334,7 +338,7 @@ bool use_keysplit(const AttnShape& s, int64_t n_rows, int64_t n_kv_rows, bool kv
   unit_counts(s, n_rows, n_kv_rows, per_req, units, tiles);
   if (kv_pos) {
     if (s.d == 128 && units > 512 && tiles <= 8) return false;
-    return units <= 1024 || (units <= 2048 && tiles >= 64);
+    return units <= 1024 || (units <= (s.d == 64 ? 2048 : 1792) && tiles >= 64);
   }
   return (double)units * (double)tiles * s.d <= 28672.0 * 128;
 }

@@ -51,3 +51,12 @@ def test_tiles_are_counted_by_the_rows_there_are():
         assert route([1250], 1536, d) == "w4"                      # short ranges
         assert route([700, 10], 1400, d) == ("stream" if d == 64 else "w4")
         assert route([1400, 10], 1536, d) == "w4"
+
+
+def test_large_probes_keep_the_shared_tile_kernel():
+    """Long probes of more than 1792 units of 32 query vectors (head size 128) fill the chip with the
+    blocks that share key tiles."""
+    route = lambda nq, kv, d: batch_route([nq] * 16, [kv] * 16, 32, 8, d, kv_pos=True)
+    assert [route(nq, 4000, 128) for nq in (64, 112, 113, 120, 128, 129)] == ["keysplit"] * 2 + ["pos"] * 4
+    assert [route(nq, 4000, 64) for nq in (128, 129)] == ["keysplit", "pos"]
+    assert route(112, 2016, 128) == "pos" and route(64, 2016, 128) == "keysplit"
