@@ -41,6 +41,9 @@ constexpr int kQv = 16;            // query vectors per block
 constexpr int kKeys = 16;          // keys per tile
 constexpr int kMaxTilesX = 1 << 20;  // blocks along x; more query tiles are strided over
 
+// a running maximum as the reference of exponentials: 0 while nothing has been seen
+__device__ __forceinline__ float finite(float m) { return m == -INFINITY ? 0.f : m; }
+
 template <int D, bool kPos>
 __global__ __launch_bounds__(kW * 64) void attn_f32_kernel(
     float* __restrict__ out, float* __restrict__ lse, const float* __restrict__ q,
@@ -100,9 +103,10 @@ __global__ __launch_bounds__(kW * 64) void attn_f32_kernel(
     f32x4 o[NB];
 #pragma unroll
     for (int mb = 0; mb < NB; ++mb) o[mb] = f32x4{};
-    // m in log2 units, shared by the four lanes of a query vector; -1e30 so that a masked
-    // logit (-inf) gives p = 0 without a guard.  ls is the lane's own keys' sum.
-    float m = -1e30f, ls = 0.f;
+    // m in log2 units, shared by the four lanes of a query vector; -inf until a key is seen
+    // (finite() keeps a masked logit's p at 0 then; any finite logit is a valid maximum).  ls is
+    // the lane's own keys' sum.
+    float m = -INFINITY, ls = 0.f;
     int kt0 = w * kKeys;
     if (kt0 < jend) {
       load_k(kt0);
@@ -149,15 +153,16 @@ __global__ __launch_bounds__(kW * 64) void attn_f32_kernel(
         mt = fmaxf(mt, __shfl_xor(mt, 16, 64));
         mt = fmaxf(mt, __shfl_xor(mt, 32, 64));
         const float mn = fmaxf(m, mt);
-        const float alpha = __builtin_amdgcn_exp2f(m - mn);
+        const float alpha = __builtin_amdgcn_exp2f(m - finite(mn));
         ls *= alpha;
 #pragma unroll
         for (int mb = 0; mb < NB; ++mb) o[mb] *= alpha;
         m = mn;
       }
       float p[4];
+      const float mr = finite(m);
 #pragma unroll
-      for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(x[r] - m);
+      for (int r = 0; r < 4; ++r) p[r] = __builtin_amdgcn_exp2f(x[r] - mr);
       ls += (p[0] + p[1]) + (p[2] + p[3]);
       const bool edge = kPos || kt0 + kKeys > wmin + 1 || kt0 + kKeys > nkv;
       bool fin = true;
@@ -212,7 +217,7 @@ __global__ __launch_bounds__(kW * 64) void attn_f32_kernel(
     const int t = threadIdx.x;
     if (t < kQv * D / 4) {
       const int i = t / (D / 4), c = 4 * (t % (D / 4));
-      float mx = -1e30f;
+      float mx = -INFINITY;
 #pragma unroll
       for (int ww = 0; ww < kW; ++ww) mx = fmaxf(mx, ml_l[ww][i].x);
       float lt = 0.f;
@@ -220,7 +225,7 @@ __global__ __launch_bounds__(kW * 64) void attn_f32_kernel(
 #pragma unroll
       for (int ww = 0; ww < kW; ++ww) {
         const float2 ml = ml_l[ww][i];
-        const float f = __builtin_amdgcn_exp2f(ml.x - mx);
+        const float f = __builtin_amdgcn_exp2f(ml.x - finite(mx));
         const float4 x = *reinterpret_cast<const float4*>(o_l + (ww * kQv + i) * OSTR + c);
         lt += f * ml.y;
         acc.x += f * x.x;

@@ -93,6 +93,28 @@ def test_attention_f32_masked_values_stay_out():
     assert not host(none).any()
 
 
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("kpos", [False, True])
+def test_attention_f32_very_negative_logits(d, kpos):
+    """Logits far below -1e30 are logits like any others: two equal largest keys share the weight."""
+    say("attention f32, very negative logits", d, kpos)
+    n, hq, hkv, scale = 300, 4, 2, 0.25
+    rng = np.random.default_rng(34)
+    v = draw(rng, (n, hkv, d), "f32")
+    k, q = np.zeros((n, hkv, d), np.float32), np.zeros((40, hq, d), np.float32)
+    q[..., 0] = 2.0 ** 57
+    k[..., 0] = -(2.0 ** 58)
+    k[[5, 150], :, 0] = -(2.0 ** 57)                # logits -2^112 for the two, -2^113 for the others
+    pos = np.full(40, n - 1, np.int32)
+    out, lse = torch.empty((40, hq, d), device="cuda"), torch.empty((40, hq), device="cuda")
+    qcf.qcf_sparse_prefill_attn(out, dev(q), dev(pos), dev(np.array([0, 40], np.int32)), dev(k), dev(v),
+                                dev(np.array([0, n], np.int32)), 40, n, scale, lse=lse,
+                                kv_pos=dev(np.arange(n, dtype=np.int32)) if kpos else None)
+    want = np.repeat((v[5].astype(np.float64) + v[150]) / 2, hq // hkv, 0)
+    np.testing.assert_allclose(host(out), np.broadcast_to(want, (40, hq, d)), rtol=1e-6, atol=1e-6)
+    np.testing.assert_allclose(lse.cpu().numpy(), -(2.0 ** 112), rtol=1e-6)
+
+
 @pytest.mark.parametrize("hq,hkv,d,ctxs,nqs,pad", [
     (8, 2, 64, [1, 15, 17, 129], [1, 4, 5, 33], 0),
     (4, 4, 128, [128, 127], [16, 17], 64),
