@@ -34,9 +34,12 @@ constexpr int kW = 8;               // waves per block
 constexpr int kTile = 16;           // query vectors and keys per tile
 constexpr int kMaxTilesX = 1 << 20;  // blocks along x; more tiles are strided over
 
+// a running maximum as the reference of exponentials: 0 while nothing has been seen
+__device__ __forceinline__ float finite(float m) { return m == -INFINITY ? 0.f : m; }
+
 __device__ __forceinline__ float2 combine_ml(float2 a, float2 b) {
-  const float m = fmaxf(a.x, b.x);
-  return make_float2(m, a.y * __builtin_amdgcn_exp2f(a.x - m) + b.y * __builtin_amdgcn_exp2f(b.x - m));
+  const float m = fmaxf(a.x, b.x), r = finite(m);
+  return make_float2(m, a.y * __builtin_amdgcn_exp2f(a.x - r) + b.y * __builtin_amdgcn_exp2f(b.x - r));
 }
 
 template <int D>
@@ -112,8 +115,8 @@ __global__ __launch_bounds__(kW * 64) void scores_stats_f32(
       f.load(kb + row * k_stride, lk);
       if constexpr (kRot) f.rotate(rot_tab + (int64_t)min(max(key_rot[row], 0), n_rot - 1) * (D / 2), lk);
     };
-    // a masked key's logit is -inf and its term 0 (the running max starts at a finite floor)
-    float m = -1e30f, ls = 0.f;
+    // a masked key's logit is -inf and its term 0; any finite logit is a valid maximum
+    float m = -INFINITY, ls = 0.f;
     int kt0 = w * kTile;
     if (kt0 < N) load_k(kf, kt0);
     // Q has to be there before the loop (a wait for it inside would count the next tile's loads)
@@ -127,10 +130,11 @@ __global__ __launch_bounds__(kW * 64) void scores_stats_f32(
 #pragma unroll
       for (int r = 0; r < 4; ++r) x[r] = kt0 + 4 * lk + r < N ? s[r] * scale2 : -INFINITY;
       const float mn = fmaxf(m, fmaxf(fmaxf(x[0], x[1]), fmaxf(x[2], x[3])));
+      const float mr = finite(mn);
       float p = 0.f;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) p += __builtin_amdgcn_exp2f(x[r] - mn);
-      ls = ls * __builtin_amdgcn_exp2f(m - mn) + p;
+      for (int r = 0; r < 4; ++r) p += __builtin_amdgcn_exp2f(x[r] - mr);
+      ls = ls * __builtin_amdgcn_exp2f(m - mr) + p;
       m = mn;
       kf = kn;
     }
@@ -145,7 +149,7 @@ __global__ __launch_bounds__(kW * 64) void scores_stats_f32(
       for (int ww = 1; ww < kW; ++ww) ml = combine_ml(ml, ml_l[ww][li]);
       if (qv < nqv && q0 + i < n_q_rows)
         stats[((int64_t)b * hq + head) * max_q_len + i] =
-            make_float2(ml.x, ml.y > 0.f ? 1.f / ml.y : 0.f);
+            make_float2(finite(ml.x), ml.y > 0.f ? 1.f / ml.y : 0.f);
     }
     __syncthreads();  // ml_l is rewritten by the next tile
   }

@@ -136,3 +136,28 @@ def test_scores_f32_edges(hq, hkv, d, ctxs, nqs, pad):
         want = Q.critical_scores(q[cu_q[b]:cu_q[b + 1]], k[a:a + n], 1 / math.sqrt(d), hkv)
         assert_scores(got[a:a + n], want, f"request {b}")
         assert np.all(got[a + n:cu_kv[b + 1]] == -5.0)
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("pic", [False, True])
+def test_scores_f32_very_negative_logits(d, pic):
+    """Logits far below -1e30 are logits like any others: two equal largest keys share the weight."""
+    say("scores f32, very negative logits", d, pic)
+    n, nq, hq, hkv = 300, 9, 4, 2
+    k, q = np.zeros((n + nq, hkv, d), np.float32), np.zeros((nq, hq, d), np.float32)
+    q[..., 0] = 2.0 ** 57
+    k[..., 0] = -(2.0 ** 58)
+    k[[5, 150], :, 0] = -(2.0 ** 57)
+    sc = torch.full((n + nq,), -5.0, device="cuda")
+    i32 = lambda *x: dev(np.array(x, np.int32))
+    geo = (i32(0, nq), i32(0, n + nq), i32(n), nq, n, 0.25)
+    if pic:
+        table = torch.empty((1, d // 2, 2), device="cuda")
+        qcf.qcf_rope_table(table, i32(0), 1e4)
+        qcf.qcf_probe_scores_pic(sc, dev(q), dev(k), dev(np.zeros(n + nq, np.int32)), table, *geo)
+    else:
+        qcf.qcf_probe_scores(sc, dev(q), dev(k), *geo)
+    want = np.zeros(n)
+    want[[5, 150]] = nq * hq / 2
+    np.testing.assert_allclose(sc.cpu().numpy()[:n], want, rtol=1e-6)
+    assert (sc[n:] == -5.0).all()
