@@ -19,7 +19,8 @@
 // both passes lane l holds row l % 16 of its operand tile and the d-columns 16 sb
 // + 4 (l / 16) + e, the contraction order of product (sb, e).  Every reduction has
 // a fixed order.  With kRot the keys are turned in registers by their rotation
-// table row (rope_pair, the arithmetic of the stored re-positioned keys).
+// table row (rope_pair, the arithmetic of the stored re-positioned keys).  exp2f, not the
+// bare instruction: weights below 2^-126 stay subnormal numbers and rank their keys.
 #include <math.h>
 
 #include <algorithm>
@@ -39,7 +40,7 @@ __device__ __forceinline__ float finite(float m) { return m == -INFINITY ? 0.f :
 
 __device__ __forceinline__ float2 combine_ml(float2 a, float2 b) {
   const float m = fmaxf(a.x, b.x), r = finite(m);
-  return make_float2(m, a.y * __builtin_amdgcn_exp2f(a.x - r) + b.y * __builtin_amdgcn_exp2f(b.x - r));
+  return make_float2(m, a.y * exp2f(a.x - r) + b.y * exp2f(b.x - r));
 }
 
 template <int D>
@@ -133,8 +134,8 @@ __global__ __launch_bounds__(kW * 64) void scores_stats_f32(
       const float mr = finite(mn);
       float p = 0.f;
 #pragma unroll
-      for (int r = 0; r < 4; ++r) p += __builtin_amdgcn_exp2f(x[r] - mr);
-      ls = ls * __builtin_amdgcn_exp2f(m - mr) + p;
+      for (int r = 0; r < 4; ++r) p += exp2f(x[r] - mr);
+      ls = ls * exp2f(m - mr) + p;
       m = mn;
       kf = kn;
     }
@@ -203,7 +204,7 @@ __global__ __launch_bounds__(kW * 64) void scores_cols_f32(
       for (int r = 0; r < 4; ++r) sv[r] = st[r];
       if (u + kW < units) load(u + kW);  // in flight during this unit's exponentials
 #pragma unroll
-      for (int r = 0; r < 4; ++r) acc += __builtin_amdgcn_exp2f(s[r] * scale2 - sv[r].x) * sv[r].y;
+      for (int r = 0; r < 4; ++r) acc += exp2f(s[r] * scale2 - sv[r].x) * sv[r].y;
     }
     acc += __shfl_xor(acc, 16, 64);
     acc += __shfl_xor(acc, 32, 64);

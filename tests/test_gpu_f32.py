@@ -161,3 +161,28 @@ def test_scores_f32_very_negative_logits(d, pic):
     want[[5, 150]] = nq * hq / 2
     np.testing.assert_allclose(sc.cpu().numpy()[:n], want, rtol=1e-6)
     assert (sc[n:] == -5.0).all()
+
+
+@pytest.mark.parametrize("d", [64, 128])
+@pytest.mark.parametrize("big", [0, 37, 299])
+def test_f32_weights_below_the_smallest_normal_number(d, big):
+    """A key whose weight is a subnormal number (e^-91 .. e^-100 of the largest) still counts: its scores
+    rank such keys, and a large value of it reaches the output."""
+    say("f32, subnormal weights", d, big)
+    n, hq, hkv = 300, 4, 2
+    gap = np.where(np.arange(n) == big, 0.0, 91.0 + np.arange(n) % 10)
+    k, q = np.zeros((n, hkv, d), np.float32), np.zeros((8, hq, d), np.float32)
+    q[..., 1], k[..., 1] = 1.0, -gap[:, None]
+    v = np.zeros((n, hkv, d), np.float32)
+    low = (big + 50) % n
+    v[low] = 1e30
+    i32 = lambda *x: dev(np.array(x, np.int32))
+    out = torch.empty((8, hq, d), device="cuda")
+    qcf.qcf_sparse_prefill_attn(out, dev(q), dev(np.full(8, n - 1, np.int32)), i32(0, 8), dev(k), dev(v),
+                                i32(0, n), 8, n, 1.0)
+    # a subnormal weight has fewer digits: at least 37.2e-45 / 1.4e-45 = 26 steps, half a step off
+    np.testing.assert_allclose(host(out), 1e30 * np.exp(-gap[low]), rtol=0.02)
+    sc = torch.empty(n + 8, device="cuda")
+    k2 = np.concatenate([k, np.zeros((8, hkv, d), np.float32)])
+    qcf.qcf_probe_scores(sc, dev(q), dev(k2), i32(0, 8), i32(0, n + 8), i32(n), 8, n, 1.0)
+    np.testing.assert_allclose(sc.double().cpu().numpy()[:n], 8 * hq * np.exp(-gap), rtol=0.02)
