@@ -71,8 +71,8 @@ __global__ __launch_bounds__(kW * 64) void attn_f32_kernel(
     const int64_t qv = tile * kQv + li;
     const int64_t grow = r0 + (qv >> lg);
     const int head = (g << lg) + (int)(qv & ((1 << lg) - 1));
-    const bool valid = qv < nqv && grow < n_rows;
-    const int64_t crow = min(grow, n_rows - 1);
+    const bool valid = qv < nqv && grow >= 0 && grow < n_rows;
+    const int64_t crow = min(max(grow, (int64_t)0), n_rows - 1);
     const int pos_raw = row_pos[crow];
     float4 qf[SB];
 #pragma unroll
@@ -237,7 +237,7 @@ __global__ __launch_bounds__(kW * 64) void attn_f32_kernel(
       }
       const int64_t ov = tile * kQv + i, orow = r0 + (ov >> lg);
       const int oh = (g << lg) + (int)(ov & ((1 << lg) - 1));
-      if (ov < nqv && orow < n_rows) {
+      if (ov < nqv && orow >= 0 && orow < n_rows) {
         const float inv = lt > 0.f ? 1.f / lt : 0.f;
         *reinterpret_cast<float4*>(out + (orow * hq + oh) * D + c) =
             make_float4(acc.x * inv, acc.y * inv, acc.z * inv, acc.w * inv);

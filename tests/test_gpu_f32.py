@@ -186,3 +186,24 @@ def test_f32_weights_below_the_smallest_normal_number(d, big):
     k2 = np.concatenate([k, np.zeros((8, hkv, d), np.float32)])
     qcf.qcf_probe_scores(sc, dev(q), dev(k2), i32(0, 8), i32(0, n + 8), i32(n), 8, n, 1.0)
     np.testing.assert_allclose(sc.double().cpu().numpy()[:n], 8 * hq * np.exp(-gap), rtol=0.02)
+
+
+def test_attention_f32_skips_rows_outside_the_tensors():
+    """Row offsets that reach before or past the rows of the call (here inside larger buffers) write
+    nothing there; the rows inside are computed."""
+    say("attention f32, rows outside the tensors")
+    rng = np.random.default_rng(35)
+    n, hq, hkv, d, rows = 70, 4, 2, 64, 20
+    k, v = (draw(rng, (n, hkv, d), "f32", 1 / math.sqrt(d)) for _ in range(2))
+    q = draw(rng, (rows + 16, hq, d), "f32", math.sqrt(d))
+    pos = rng.integers(0, n, rows + 16).astype(np.int32)
+    out, lse = torch.full((rows + 16, hq, d), 7.0, device="cuda"), torch.full((rows + 16, hq), 7.0, device="cuda")
+    inner = slice(8, 8 + rows)
+    qcf.qcf_sparse_prefill_attn(out[inner], dev(q)[inner], dev(pos)[inner], dev(np.array([-8, rows + 8], np.int32)),
+                                dev(k), dev(v), dev(np.array([0, n], np.int32)), rows + 16, n, 1 / math.sqrt(d),
+                                lse=lse[inner])
+    want = Q.attention(q[inner], pos[inner], k, v, np.arange(n), 1 / math.sqrt(d), hkv)
+    got = host(out)
+    assert_close(got[inner], want, "f32", "rows inside")
+    assert np.all(got[:8] == 7.0) and np.all(got[8 + rows:] == 7.0)
+    assert (lse[:8] == 7.0).all() and (lse[8 + rows:] == 7.0).all()
