@@ -81,15 +81,19 @@ inline RopeFreq rope_freq(double theta, int d) {
 
 // The (cos, sin) of pos * omega_j, formed in float64 and rounded to float32.  The angle is reduced
 // by multiples of pi/2 (two-part constant, one fused multiply-add each: exact to float64 rounding
-// for angles below 2^52, which every position reaches only with theta < 1e-6) and both functions
-// come from their Taylor series on [-pi/4, pi/4] (first omitted terms below 1e-16).  With the
+// for angles below 2^52; larger ones, which take theta < 1e-6, go through the library) and both
+// functions come from their Taylor series on [-pi/4, pi/4] (first omitted terms below 1e-16).  With the
 // library's pow and sincos a block's start took longer: assembling a 32K-token request 58.7 ->
 // 56.1 us, a layer recompute of 10 x 512 tokens ~1 us less in each of its two rotations.
 __device__ __forceinline__ float2 rope_cs(double pos, int j, const RopeFreq& fr) {
   double x = pos;
 #pragma unroll
   for (int i = 0; i < 6; ++i) x = (j >> i) & 1 ? x * fr.f[i] : x;
-  if (!(fabs(x) < 0x1p52)) x -= x;  // no digit after the point is left: 0; infinity, NaN: NaN
+  if (!(fabs(x) < 0x1p52)) {  // (the library's reduction; infinity, NaN: NaN)
+    double s, c;
+    sincos(x, &s, &c);
+    return make_float2((float)c, (float)s);
+  }
   const double k = rint(x * 0x1.45f306dc9c883p-1);  // 2 / pi
   double r = fma(-k, 0x1.921fb54442d18p+0, x);
   r = fma(-k, 0x1.1a62633145c07p-54, r);

@@ -341,6 +341,21 @@ def test_rope_table():
         np.testing.assert_array_equal(got[0], np.stack([np.ones(d // 2), np.zeros(d // 2)], -1))
 
 
+@pytest.mark.parametrize("d", [64, 128])
+def test_rope_table_large_angles(d):
+    """theta = 2^-64 makes every frequency a power of two, so the angles, up to 2^93, are exact in
+    float64 and the table has their sine and cosine; theta = 1/4 reaches 2^33."""
+    say("rope table, large angles", d)
+    pos = np.array([0, 1, 3, 1000, -7, 123456789, -2 ** 31, 2 ** 31 - 1], np.int32)
+    for bits, tol in ((64, 1e-7), (2, 2e-6)):
+        table = torch.empty((pos.size, d // 2, 2), device="cuda")
+        qcf.qcf_rope_table(table, dev(pos), 2.0 ** -bits)
+        angle = [[float(p) * 2.0 ** (2 * bits * j / d) for j in range(d // 2)] for p in pos.tolist()]
+        want = np.array([[(math.cos(a), math.sin(a)) for a in row] for row in angle])
+        # float32 rounding of a value in [-1, 1]; with 1/4 the angle's own rounding, 2^33 x 3e-16
+        assert np.abs(table.double().cpu().numpy() - want).max() < tol
+
+
 @pytest.mark.parametrize("dtype,nqs,ctxs,hq,hkv,d,pad", [
     ("bf16", [64], [5120], 32, 8, 128, 128),            # 10 x 512-token chunks, padded rows
     ("bf16", [17, 1, 128], [700, 3000, 129], 32, 8, 128, 0),
