@@ -134,6 +134,16 @@ __global__ __launch_bounds__(KW * 64) void attn_keysplit_kernel(
       st16(kl + (c / CPR) * KSTR + (c % CPR) * 8, kt[i]);
       st16(vl + (c / CPR) * VSTR + (c % CPR) * 8, vt[i]);
     }
+    if (!kPos && kt0 + kKeys > nkv) {
+      // rows past the last key repeat it: their weight is 0, and 0 times a value that is not finite
+      // must not reach the rows that see that key (probes, as in the shared-tile kernel, keep the
+      // repeated rows: 2% of a 700-key probe)
+#pragma unroll
+      for (int i = 0; i < TL; ++i) {
+        const int c = i * 64 + l;
+        if (kt0 + c / CPR >= nkv) st16(vl + (c / CPR) * VSTR + (c % CPR) * 8, make_uint4(0, 0, 0, 0));
+      }
+    }
     const int kpc = kt0 + lq < nkv ? kp : INT_MAX;
     asm volatile("" ::: "memory");  // (a wave's LDS accesses execute in order)
     if (t + KW < t_hi) load(kt0 + KW * kKeys);  // in flight during this tile's work

@@ -9,6 +9,7 @@ import torch
 from oracle import qcfuse as Q
 from paper_2606_05875_amd import qcf
 from parity import assert_close
+from routes import batch_route
 from test_gpu_kernels import dev, draw, host, padded, say
 
 pytestmark = pytest.mark.gpu
@@ -92,3 +93,28 @@ def test_keysplit_cut_key_ranges(hq, hkv, d, n_kv, n_rows, mode):
         qcf.qcf_sparse_prefill_attn(o, q, pos, cu[0], k, v, cu[1], n_rows[0], n_kv[0], 0.1, workspace=w)
         outs.append(o)
     assert torch.equal(outs[0], outs[1]) and torch.equal(outs[0], outs[2])
+
+
+@pytest.mark.parametrize("mode", ["causal", "rope"])
+@pytest.mark.parametrize("d,n", [(64, 1), (64, 33), (128, 40), (128, 290)])
+def test_keysplit_infinite_last_value(d, n, mode):
+    """An infinite value of the last key gives infinity, and nothing else, to the rows that see it: the
+    rest of its tile holds no key."""
+    say("key-split attention, infinite last value", mode, d, n)
+    rng = np.random.default_rng(43)
+    hq, hkv, rows = 8, 2, 9
+    k, v = (draw(rng, (n, hkv, d), "bf16", 0.1) for _ in range(2))
+    v[n - 1, 1, 5] = np.inf
+    q = dev(draw(rng, (rows, hq, d), "bf16", 1.0), torch.bfloat16)
+    out = torch.empty_like(q)
+    assert batch_route([rows], [n], hq, hkv, d) == "keysplit"
+    geo = (dev(np.full(rows, n - 1, np.int32)), dev(np.array([0, rows], np.int32)), dev(k, torch.bfloat16),
+           dev(v, torch.bfloat16), dev(np.array([0, n], np.int32)), rows, n, 0.1)
+    if mode == "rope":
+        qcf.qcf_sparse_prefill_attn_rope(out, q, *geo, qcf.rope_position_table(n, d, 1e6))
+    else:
+        qcf.qcf_sparse_prefill_attn(out, q, *geo)
+    got = host(out)
+    assert np.all(got[:, hq // 2:, 5] == np.inf)
+    got[:, hq // 2:, 5] = 0
+    assert np.isfinite(got).all()
