@@ -1217,7 +1217,8 @@ AttnRoute attn_route(const AttnShape& shape, int64_t n_rows, int64_t n_kv_rows, 
     return w4 ? AttnRoute::kW4 : AttnRoute::kStream;
   }
   const int64_t cus = cu_count();
-  if (ws && s.batch == 1 && pad256 >= 4 * cus && pad256 + pad256 / 8 <= 0x7fffffff)
+  // (a call of at most one key tile needs no workspace: the one it may come with can be too small)
+  if (ws && s.max_kv > kKT && s.batch == 1 && pad256 >= 4 * cus && pad256 + pad256 / 8 <= 0x7fffffff)
     return AttnRoute::kQueue;
   return few && most256 <= cus + s.hkv ? AttnRoute::kPlain : AttnRoute::kW4;
 }

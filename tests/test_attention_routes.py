@@ -60,3 +60,15 @@ def test_large_probes_keep_the_shared_tile_kernel():
     assert [route(nq, 4000, 128) for nq in (64, 112, 113, 120, 128, 129)] == ["keysplit"] * 2 + ["pos"] * 4
     assert [route(nq, 4000, 64) for nq in (128, 129)] == ["keysplit", "pos"]
     assert route(112, 2016, 128) == "pos" and route(64, 2016, 128) == "keysplit"
+
+
+def test_work_queues_need_a_workspace_that_was_asked_for():
+    """The counters of the work queues lie in the workspace: a call that needs none (at most 64 keys)
+    may come with a smaller one, so it never takes them."""
+    for rows in (8000, 20000):
+        args = dict(batch=1, max_rows=rows, hq=64, hkv=8, d=128, n_rows=rows)
+        assert qcf.qcf_sparse_prefill_attn_workspace_size(1, rows, 64, 64, 8, 128) == 0
+        assert attn_route(max_kv=64, n_kv_rows=64, **args) == "w4"
+        assert qcf.qcf_sparse_prefill_attn_workspace_size(1, rows, 129, 64, 8, 128) > 0
+        assert attn_route(max_kv=129, n_kv_rows=129, **args) == "queue"
+        assert attn_route(max_kv=129, n_kv_rows=129, ws=False, **args) == "w4"
