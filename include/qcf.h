@@ -349,15 +349,16 @@ qcf_status qcf_probe_scores_select_noalloc(float* scores, int accumulate, const 
  *        workspace then holds the work plan and the partial results of row tiles
  *        cut between two blocks, which a second kernel merges in a fixed order
  *        (deterministic).  A bf16 call with very few query vectors over long key
- *        ranges cuts the ranges over blocks and merges their partial results from
- *        the workspace in the same way; without room for them it runs uncut.  A bf16 call without kv_pos over one request with at
- *        least four row tiles per compute unit hands the tiles out from work
- *        counters in the workspace, which the call resets itself (by a kernel on
- *        the same stream); each tile is still computed whole by one block, so the
- *        result does not depend on which block takes it.  Its contents need no
- *        initialisation; calls that overlap in time need separate workspaces.  The size query is monotone: the size
- *        for (batch, max_rows, max_kv) covers every call whose three values do
- *        not exceed them (other arguments equal).
+ *        ranges, with or without kv_pos, cuts the ranges over blocks and merges their
+ *        partial results from the workspace in the same way.  A bf16 call without
+ *        kv_pos over one request with at least four row tiles per compute unit hands
+ *        the tiles out from work counters in the workspace, which the call resets
+ *        itself (by a kernel on the same stream); each tile is still computed whole
+ *        by one block, so the result does not depend on which block takes it.  The
+ *        workspace's contents need no initialisation; calls that overlap in time
+ *        need separate workspaces.  The size query is monotone: the size for
+ *        (batch, max_rows, max_kv) covers every call whose three values do not
+ *        exceed them (other arguments equal).
  */
 size_t qcf_sparse_prefill_attn_workspace_size(int batch, int max_rows, int max_kv,
                                               int n_q_heads, int n_kv_heads, int head_dim,

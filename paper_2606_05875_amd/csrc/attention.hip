@@ -1248,11 +1248,9 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
   if (bf16 && !kv_pos && (double)s.max_kv * (double)kv_row_stride * 2.0 >= 2147483648.0)
     return hipErrorInvalidConfiguration;
   const AttnRoute route = attn_route(shape, n_rows, n_kv_rows, bf16, kv_pos != nullptr, ws != nullptr);
-  // the workspace holds stream_layout's bytes whenever attn_workspace asks for one
   if (route == AttnRoute::kKeySplit)
     return launch_attn_keysplit(out, lse, q, row_pos, n_rows, cu_rows, k_cache, v_cache, n_kv_rows,
-                                kv_row_stride, cu_kv, kv_pos, s, scale, ws,
-                                ws ? attn_workspace(s, true) : 0, stream, qrot);
+                                kv_row_stride, cu_kv, kv_pos, s, scale, ws, stream, qrot);
   if (route == AttnRoute::kW4)
     return launch_attn_w4(out, lse, q, row_pos, n_rows, cu_rows, k_cache, v_cache, n_kv_rows,
                           kv_row_stride, cu_kv, s, scale, stream, qrot);

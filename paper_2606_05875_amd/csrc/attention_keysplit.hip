@@ -119,7 +119,9 @@ __global__ __launch_bounds__(KW * 64) void attn_keysplit_kernel(
   f32x16 o[D / 32];
 #pragma unroll
   for (int mb = 0; mb < D / 32; ++mb) o[mb] = f32x16{};
-  float m = valid ? -1e30f : INFINITY;  // log2 units; padding lanes never rescale and give p = 0
+  // log2 units.  A padding lane never asks for a rescale, but its alpha in one is inf - inf: its
+  // sum and O may be NaN, stay in its own column to the end (partials too) and are never used.
+  float m = valid ? -1e30f : INFINITY;
   float ls = 0.f;
   if (t < t_hi) load(t * kKeys);
   // Q has to be there before the loop: the compiler's wait for it at the products would count
@@ -357,24 +359,25 @@ hipError_t launch_attn_keysplit(void* out, float* lse, const void* q, const int3
                                 int64_t n_rows, const int32_t* cu_rows, const void* k_cache,
                                 const void* v_cache, int64_t n_kv_rows, int64_t kv_row_stride,
                                 const int32_t* cu_kv, const int32_t* kv_pos, const AttnShape& s,
-                                float scale, void* ws, size_t ws_bytes, hipStream_t stream,
+                                float scale, void* ws, hipStream_t stream,
                                 const QueryRot& qrot) {
   int lg = 0;
   while ((1 << lg) < s.hq / s.hkv) ++lg;
   int64_t max_units, units, tiles;
   unit_counts(s, n_rows, n_kv_rows, max_units, units, tiles);
-  // Waves per block: 8 where a wave gets several tiles; short key ranges take smaller blocks
-  // (less LDS, so more of them, or another stream's blocks, fit beside each other on a CU and
-  // hide each other's start).  2048 units x 9 tiles: 45.5, 42.6, 31.6 us with 8, 4, 2 waves;
+  // Waves per block: 8 where a wave gets several tiles; short key ranges take smaller blocks, which
+  // start and combine for fewer waves.  (At head size 64 they also fit beside each other on a CU;
+  // at 128 the smaller forms take more than 256 registers, accumulators included, so a SIMD holds
+  // one wave of them: one 4-wave or two 2-wave blocks per CU.)  2048 units x 9 tiles: 45.5, 42.6, 31.6 us with 8, 4, 2 waves;
   // 64 x 9: 8.3, 8.2, 9.3; 64 x 35: 14.3, 16.2, 25.0; 371 x 34: 32.7, 35.0, 35.2.
   const int KW = tiles >= 32 ? 8 : units <= 512 ? 4 : 2;
   // Key ranges are cut over blocks where units leave three quarters of the CUs idle and a
   // cut wave still has two tiles (64 units x 322 tiles: 69 -> 30 us with 4 cuts, 36 with 8;
-  // 8 x 130: 20.7 -> 10.8; 64 x 35: no gain, the merge costs what it saves).
+  // 8 x 130: 20.7 -> 10.8; 64 x 35: no gain, the merge costs what it saves).  At most 256 partials:
+  // the workspace that a call of more than 64 keys brings always holds them.
   int n_split = 1;
   if (units * 4 <= 256 && tiles >= 64)
     n_split = (int)std::min<int64_t>(std::min<int64_t>(kMaxSplit, 256 / units), tiles / 16);
-  if ((size_t)units * n_split * kQv * (s.d * 4 + 8) > ws_bytes) n_split = 1;
   const size_t slots = (size_t)units * n_split;
   float4* part_o = static_cast<float4*>(ws);
   float2* part_ml = reinterpret_cast<float2*>(static_cast<char*>(ws) + slots * kQv * s.d * 4);
@@ -401,7 +404,7 @@ hipError_t launch_attn_keysplit(void* out, float* lse, const void* q, const int3
     else if (KW == 4) QCF_KSK(D, 4);                                                               \
     else QCF_KSK(D, 2);                                                                            \
     if (n_split > 1)                                                                               \
-      attn_keysplit_merge_kernel<D><<<dim3((unsigned)(units * (D / 32))), 256, 0, \
+      attn_keysplit_merge_kernel<D><<<dim3((unsigned)(units * (D / 32))), 256, 0,               \
                                       stream>>>(static_cast<uint16_t*>(out), lse, n_rows, cu_rows,  \
                                                 (int)max_units, s.hkv, s.hq, lg, n_split,           \
                                                 part_o, part_ml);                                  \

@@ -144,7 +144,7 @@ hipError_t launch_attn_keysplit(void* out, float* lse, const void* q, const int3
                                 int64_t n_rows, const int32_t* cu_rows, const void* k_cache,
                                 const void* v_cache, int64_t n_kv_rows, int64_t kv_row_stride,
                                 const int32_t* cu_kv, const int32_t* kv_pos, const AttnShape& s,
-                                float scale, void* ws, size_t ws_bytes, hipStream_t stream,
+                                float scale, void* ws, hipStream_t stream,
                                 const QueryRot& qrot);
 // bf16 recomputed rows on 4-wave blocks, one per row tile
 hipError_t launch_attn_w4(void* out, float* lse, const void* q, const int32_t* row_pos,

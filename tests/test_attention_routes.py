@@ -72,3 +72,12 @@ def test_work_queues_need_a_workspace_that_was_asked_for():
         assert qcf.qcf_sparse_prefill_attn_workspace_size(1, rows, 129, 64, 8, 128) > 0
         assert attn_route(max_kv=129, n_kv_rows=129, **args) == "queue"
         assert attn_route(max_kv=129, n_kv_rows=129, ws=False, **args) == "w4"
+
+
+def test_workspace_holds_the_partials_of_cut_key_ranges():
+    """Key ranges are cut into at most 256 partials of 32 query vectors (float32, and two floats each);
+    every call long enough to be cut (2017 keys and more) needs a workspace that holds them."""
+    for hkv in list(range(1, 260)) + [1000, 65535]:
+        for d in (64, 128):
+            need = qcf.qcf_sparse_prefill_attn_workspace_size(1, 1, 2017, hkv, hkv, d)
+            assert need >= 256 * 32 * (4 * d + 8), (hkv, d)
