@@ -355,6 +355,17 @@ bool use_keysplit(const AttnShape& s, int64_t n_rows, int64_t n_kv_rows, bool kv
   return (double)units * (double)tiles * s.d <= 28672.0 * 128;
 }
 
+// Waves per block: 8 where a wave gets several tiles; short key ranges take smaller blocks, which
+// start and combine for fewer waves.  (At head size 64 they also fit beside each other on a CU;
+// at 128 the smaller forms take more than 256 registers, accumulators included, so a SIMD holds
+// one wave of them: one 4-wave or two 2-wave blocks per CU.)  2048 units x 9 tiles: 45.5, 42.6, 31.6 us with 8, 4, 2 waves;
+// 64 x 9: 8.3, 8.2, 9.3; 64 x 35: 14.3, 16.2, 25.0; 371 x 34: 32.7, 35.0, 35.2.
+int keysplit_waves(const AttnShape& s, int64_t n_rows, int64_t n_kv_rows) {
+  int64_t per_req, units, tiles;
+  unit_counts(s, n_rows, n_kv_rows, per_req, units, tiles);
+  return tiles >= 32 ? 8 : units <= 512 ? 4 : 2;
+}
+
 hipError_t launch_attn_keysplit(void* out, float* lse, const void* q, const int32_t* row_pos,
                                 int64_t n_rows, const int32_t* cu_rows, const void* k_cache,
                                 const void* v_cache, int64_t n_kv_rows, int64_t kv_row_stride,
@@ -365,12 +376,7 @@ hipError_t launch_attn_keysplit(void* out, float* lse, const void* q, const int3
   while ((1 << lg) < s.hq / s.hkv) ++lg;
   int64_t max_units, units, tiles;
   unit_counts(s, n_rows, n_kv_rows, max_units, units, tiles);
-  // Waves per block: 8 where a wave gets several tiles; short key ranges take smaller blocks, which
-  // start and combine for fewer waves.  (At head size 64 they also fit beside each other on a CU;
-  // at 128 the smaller forms take more than 256 registers, accumulators included, so a SIMD holds
-  // one wave of them: one 4-wave or two 2-wave blocks per CU.)  2048 units x 9 tiles: 45.5, 42.6, 31.6 us with 8, 4, 2 waves;
-  // 64 x 9: 8.3, 8.2, 9.3; 64 x 35: 14.3, 16.2, 25.0; 371 x 34: 32.7, 35.0, 35.2.
-  const int KW = tiles >= 32 ? 8 : units <= 512 ? 4 : 2;
+  const int KW = keysplit_waves(s, n_rows, n_kv_rows);
   // Key ranges are cut over blocks where units leave three quarters of the CUs idle and a
   // cut wave still has two tiles (64 units x 322 tiles: 69 -> 30 us with 4 cuts, 36 with 8;
   // 8 x 130: 20.7 -> 10.8; 64 x 35: no gain, the merge costs what it saves).  At most 256 partials:

@@ -140,6 +140,7 @@ hipError_t launch_attn_f32(float* out, float* lse, const float* q, const int32_t
                            float scale, hipStream_t stream);
 // bf16 calls with few query vectors: blocks whose waves split the keys
 bool use_keysplit(const AttnShape& s, int64_t n_rows, int64_t n_kv_rows, bool kv_pos);
+int keysplit_waves(const AttnShape& s, int64_t n_rows, int64_t n_kv_rows);  // per block
 hipError_t launch_attn_keysplit(void* out, float* lse, const void* q, const int32_t* row_pos,
                                 int64_t n_rows, const int32_t* cu_rows, const void* k_cache,
                                 const void* v_cache, int64_t n_kv_rows, int64_t kv_row_stride,

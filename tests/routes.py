@@ -18,6 +18,14 @@ def attn_route(batch, max_rows, max_kv, hq, hkv, d, n_rows, n_kv_rows, bf16=True
     return NAMES[fn(_Shape(batch, max_rows, max_kv, hq, hkv, d), n_rows, n_kv_rows, bf16, kv_pos, ws)]
 
 
+def keysplit_waves(n_rows, n_kv, hq, hkv, d):
+    """Waves per block of the key-split kernel for such a batch."""
+    fn = qcf.lib()["_ZN3qcf14keysplit_wavesERKNS_9AttnShapeEll"]
+    fn.restype = ctypes.c_int
+    fn.argtypes = [ctypes.POINTER(_Shape), ctypes.c_long, ctypes.c_long]
+    return fn(_Shape(len(n_kv), max(n_rows), max(n_kv), hq, hkv, d), sum(n_rows), sum(n_kv))
+
+
 def batch_route(n_rows, n_kv, hq, hkv, d, **kw):
     """The route of a batch of requests with n_rows[b] rows over n_kv[b] keys each."""
     return attn_route(len(n_kv), max(n_rows), max(n_kv), hq, hkv, d, sum(n_rows), sum(n_kv), **kw)

@@ -15,6 +15,7 @@ from oracle import qcfuse as Q
 from paper_2606_05875_amd import qcf
 from paper_2606_05875_amd.workloads import round_to_bf16
 from parity import assert_close, assert_scores, assert_ulp
+from routes import batch_route
 
 pytestmark = pytest.mark.gpu
 DT = {"bf16": torch.bfloat16, "f32": torch.float32}
@@ -456,12 +457,18 @@ def test_sparse_attention(dtype, hq, hkv, d, n_kv, n_rows):
             assert abs(float(lse[r, h]) - want_lse) < 2e-3 * max(1.0, abs(want_lse))
 
 
-def test_attention_explicit_positions_and_batch():
-    say("attention explicit positions, batch of 3")
+@pytest.mark.parametrize("hq,hkv,d,n_kv,n_rows,route", [
+    (32, 8, 128, [200, 37, 1100], [64, 1, 40], "keysplit"),
+    # many query vectors: the kernel that shares key tiles (short ranges at head size 128 sooner)
+    (32, 8, 128, [200, 64, 130, 1, 251], [128, 100, 1, 7, 120], "pos"),
+    (64, 8, 128, [300, 65, 2, 128, 700], [128, 60, 33, 1, 128], "pos"),
+    (32, 8, 64, [200, 63, 130, 1, 251, 64, 65, 300, 40], [128, 100, 1, 7, 120, 128, 0, 77, 64], "pos"),
+    (8, 8, 64, [500, 190, 1000, 33, 70], [1000, 700, 129, 1, 300], "pos"),
+])
+def test_attention_explicit_positions_and_batch(hq, hkv, d, n_kv, n_rows, route):
+    say("attention explicit positions, batch", hq, hkv, d, n_kv, n_rows, route)
+    assert batch_route(n_rows, n_kv, hq, hkv, d, kv_pos=True) == route
     rng = np.random.default_rng(7)
-    hq, hkv, d = 32, 8, 128
-    n_kv = [200, 37, 1100]
-    n_rows = [64, 1, 40]
     cu_kv = np.concatenate([[0], np.cumsum(n_kv)]).astype(np.int32)
     cu_r = np.concatenate([[0], np.cumsum(n_rows)]).astype(np.int32)
     k = draw(rng, (cu_kv[-1], hkv, d), "bf16", 1 / math.sqrt(d))
@@ -474,8 +481,10 @@ def test_attention_explicit_positions_and_batch():
                                 dev(v, torch.bfloat16), dev(cu_kv), max(n_rows), max(n_kv), 1 / math.sqrt(d),
                                 kv_pos=dev(kpos))
     got = host(out)
-    for b in range(3):
+    for b in range(len(n_kv)):
         a, e, ka, ke = cu_r[b], cu_r[b + 1], cu_kv[b], cu_kv[b + 1]
+        if e == a:
+            continue
         want = Q.round_storage(Q.attention(q[a:e], rpos[a:e], k[ka:ke], v[ka:ke], kpos[ka:ke],
                                            1 / math.sqrt(d), hkv), "bf16")
         assert_close(got[a:e], want, "bf16", f"request {b}")
@@ -496,10 +505,10 @@ def test_empty_calls():
 
 @pytest.mark.parametrize("hq,hkv,d", [(16, 2, 64), (8, 8, 64), (32, 8, 128)])
 def test_attention_plain_grid_every_tile(hq, hkv, d):
-    """The plain grid (one block per row tile, each block's two wave groups on their own
-    schedules: waves 0-3 multiply a tile's P.V in its own step, waves 4-7 in the next one) at
-    head sizes 64 and 128 and group sizes 8, 1 and 4: the first and last row of every row tile
-    of a ragged batch against the oracle."""
+    """The plain grid of 8-wave blocks (one block per row tile, each block's two wave groups on
+    their own schedules: waves 0-3 multiply a tile's P.V in its own step, waves 4-7 in the next
+    one) at head sizes 64 and 128 and group sizes 8, 1 and 4: the first and last row of every row
+    tile of a ragged batch, whose rows sit mostly in its first request, against the oracle."""
     say("attention plain grid", hq, hkv, d)
     rng = np.random.default_rng(9)
     g = hq // hkv
@@ -507,8 +516,7 @@ def test_attention_plain_grid_every_tile(hq, hkv, d):
     first_tiles = -(-512 // (4 * hkv))             # enough row tiles for the plain grid
     n_rows = [first_tiles * rpb + 5, 9 * rpb, 3 * rpb + 1, rpb - 7]
     n_kv = [r * 3 // 2 + 40 for r in n_rows]
-    tiles = (max(n_rows) + rpb - 1) // rpb
-    assert tiles * len(n_kv) * hkv >= 384, "the case must take the plain grid"
+    assert batch_route(n_rows, n_kv, hq, hkv, d) == "plain"
     cu_kv = np.concatenate([[0], np.cumsum(n_kv)]).astype(np.int32)
     cu_r = np.concatenate([[0], np.cumsum(n_rows)]).astype(np.int32)
     k = draw(rng, (cu_kv[-1], hkv, d), "bf16", 1 / math.sqrt(d))
@@ -535,13 +543,15 @@ def test_attention_one_request_work_queues(hq, hkv, d):
     """One request with four row tiles per CU (1024 blocks of 32 rows x 8 query heads) takes its
     tiles from the per-XCD work queues (8 KV heads: one per queue; 2: four XCDs per queue; 16:
     two heads per queue).  The same call laid out as a batch of two (the second request empty)
-    runs the fixed one-block-per-tile order: every row must match it bit for bit, on two calls
+    runs on 4-wave blocks in a fixed order: every row must match it bit for bit, on two calls
     in a row (the counters are reset by the call itself) and with a dirty workspace; sampled
     rows (the last tile, the first, every 16th) also match the oracle.  Head sizes 128 and 64."""
     rpb = 256 // (hq // hkv)
     n_rows = 4 * 256 * rpb // hkv                    # 1024 blocks: the queue threshold on 256 CUs
     n_kv = n_rows + n_rows // 2
     say("attention work queues", hq, hkv, d, n_rows, n_kv)
+    assert batch_route([n_rows], [n_kv], hq, hkv, d) == "queue"
+    assert batch_route([n_rows, 0], [n_kv, 0], hq, hkv, d) == "w4"
     rng = np.random.default_rng(21)
     k = draw(rng, (n_kv, hkv, d), "bf16", 1 / math.sqrt(d))
     v = draw(rng, (n_kv, hkv, d), "bf16", 1 / math.sqrt(d))
@@ -592,16 +602,20 @@ def test_attention_one_request_work_queues(hq, hkv, d):
         assert torch.equal(eager, ref)
 
 
-@pytest.mark.parametrize("n_kv,n_rows,plain", [
-    ([2500, 2500, 400, 3100, 1200, 64], [700, 700, 90, 650, 0, 64], True),
-    ([300, 1200, 50, 1200], [100, 400, 10, 0], False)])
-def test_attention_ragged_batch(n_kv, n_rows, plain):
+@pytest.mark.parametrize("hq,hkv,d,n_kv,n_rows,rot,route", [
+    (32, 8, 128, [2500, 2500, 400, 3100, 1200, 64], [700, 700, 90, 650, 0, 64], False, "w4"),
+    (32, 8, 128, [300, 2400, 50, 2400], [100, 400, 10, 0], False, "stream"),
+    (32, 8, 128, [300, 2400, 50, 2400], [100, 400, 10, 0], True, "stream"),
+    (64, 8, 64, [300, 2400, 1, 1700], [64, 300, 1, 290], False, "stream"),
+    (16, 4, 64, [2000, 0, 2400, 129], [900, 0, 800, 120], True, "stream")])
+def test_attention_ragged_batch(hq, hkv, d, n_kv, n_rows, rot, route):
     """A ragged batch on both grids: one block per row tile (many tiles; requests taken longest
-    first) and the persistent grid (few tiles; cut tiles merged); equal-length requests, a
-    request with no rows and a short one; sampled rows against the oracle."""
-    say("attention ragged batch", n_kv, n_rows, "plain" if plain else "persistent")
+    first) and the persistent grid (few tiles; cut tiles merged), at both head sizes and with
+    queries rotated in the kernel; equal-length requests, a request with no rows and a short one;
+    sampled rows against the oracle."""
+    say("attention ragged batch", hq, hkv, d, n_kv, n_rows, rot, route)
+    assert batch_route(n_rows, n_kv, hq, hkv, d) == route
     rng = np.random.default_rng(8)
-    hq, hkv, d = 32, 8, 128
     cu_kv = np.concatenate([[0], np.cumsum(n_kv)]).astype(np.int32)
     cu_r = np.concatenate([[0], np.cumsum(n_rows)]).astype(np.int32)
     k = draw(rng, (cu_kv[-1], hkv, d), "bf16", 1 / math.sqrt(d))
@@ -609,12 +623,15 @@ def test_attention_ragged_batch(n_kv, n_rows, plain):
     q = draw(rng, (cu_r[-1], hq, d), "bf16", math.sqrt(d))
     rpos = np.concatenate([np.sort(rng.choice(nk, nr, replace=False)) for nk, nr in zip(n_kv, n_rows)])
     rpos = rpos.astype(np.int32)
-    # the grid choice: one block per (row tile, request, KV head) from 384 such blocks on
-    assert ((max(n_rows) + 63) // 64 * len(n_kv) * hkv >= 384) == plain
     out = torch.empty((cu_r[-1], hq, d), dtype=torch.bfloat16, device="cuda")
     scale = 1 / math.sqrt(d)
-    qcf.qcf_sparse_prefill_attn(out, dev(q, torch.bfloat16), dev(rpos), dev(cu_r), dev(k, torch.bfloat16),
-                                dev(v, torch.bfloat16), dev(cu_kv), max(n_rows), max(n_kv), scale)
+    geo = (dev(q, torch.bfloat16), dev(rpos), dev(cu_r), dev(k, torch.bfloat16), dev(v, torch.bfloat16),
+           dev(cu_kv), max(n_rows), max(n_kv), scale)
+    if rot:
+        qcf.qcf_sparse_prefill_attn_rope(out, *geo, qcf.rope_position_table(max(n_kv), d, 1e6))
+        q = Q.round_storage(Q.rope(q, rpos, 1e6), "bf16")
+    else:
+        qcf.qcf_sparse_prefill_attn(out, *geo)
     got = host(out)
     for b in range(len(n_kv)):
         a, e, ka, ke = cu_r[b], cu_r[b + 1], cu_kv[b], cu_kv[b + 1]

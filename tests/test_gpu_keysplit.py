@@ -9,7 +9,7 @@ import torch
 from oracle import qcfuse as Q
 from paper_2606_05875_amd import qcf
 from parity import assert_close
-from routes import batch_route
+from routes import batch_route, keysplit_waves
 from test_gpu_kernels import dev, draw, host, padded, say
 
 pytestmark = pytest.mark.gpu
@@ -55,17 +55,21 @@ def _attn(hq, hkv, d, n_kv, n_rows, pad, kpos, rot):
 
 
 # head groups 1 to 32; one key, one less, exactly and one more than a tile; rows that fill a unit
-# partly; a request without rows; 8, 4 and 2 waves per block (few units; more; many short ones)
+# partly; a request without rows; 8, 4 and 2 waves per block (long ranges; few units; many short ones)
 @pytest.mark.parametrize("mode", ["causal", "rope", "positions"])
-@pytest.mark.parametrize("hq,hkv,d,n_kv,n_rows,pad", [
-    (8, 2, 64, [1, 31, 32, 33, 300], [1, 7, 8, 9, 20], 0),
-    (4, 4, 128, [257, 1100], [31, 64], 64),
-    (32, 1, 64, [90, 40], [2, 0], 8),
-    (32, 8, 128, [100, 70, 33], [65, 33, 3], 128),      # 4 waves per block
-    (64, 8, 128, [64, 120, 16], [40, 64, 1], 0),        # 2 waves per block
+@pytest.mark.parametrize("hq,hkv,d,n_kv,n_rows,pad,waves", [
+    (8, 2, 64, [1, 31, 32, 33, 300], [1, 7, 8, 9, 20], 0, 4),
+    (4, 4, 128, [257, 1100], [31, 64], 64, 8),
+    (16, 4, 64, [993, 40], [33, 7], 0, 8),
+    (32, 1, 64, [90, 40], [2, 0], 8, 4),
+    (32, 8, 128, [100, 70, 33], [65, 33, 3], 128, 4),
+    (64, 8, 128, [300, 257, 64, 33, 290], [40, 64, 1, 33, 64], 0, 2),
+    (32, 8, 64, [257, 1, 64, 290, 33, 160, 31, 300, 32], [64, 1, 33, 60, 64, 7, 31, 64, 17], 64, 2),
 ])
-def test_keysplit_edges(hq, hkv, d, n_kv, n_rows, pad, mode):
-    say("key-split attention", mode, hq, hkv, d, n_kv, n_rows, pad)
+def test_keysplit_edges(hq, hkv, d, n_kv, n_rows, pad, waves, mode):
+    say("key-split attention", mode, hq, hkv, d, n_kv, n_rows, pad, waves)
+    assert batch_route(n_rows, n_kv, hq, hkv, d, kv_pos=mode == "positions") == "keysplit"
+    assert keysplit_waves(n_rows, n_kv, hq, hkv, d) == waves
     _attn(hq, hkv, d, n_kv, n_rows, pad, mode == "positions", mode == "rope")
 
 
@@ -79,6 +83,7 @@ def test_keysplit_cut_key_ranges(hq, hkv, d, n_kv, n_rows, mode):
     """Key ranges cut over blocks: the partials are merged in order, so two calls over a dirty
     workspace agree bit for bit, and the result matches the oracle."""
     say("key-split attention, cut", mode, hq, hkv, d, n_kv, n_rows)
+    assert batch_route(n_rows, n_kv, hq, hkv, d, kv_pos=mode == "positions") == "keysplit"
     _attn(hq, hkv, d, n_kv, n_rows, 0, mode == "positions", False)
     rng = np.random.default_rng(42)
     k, v = (dev(draw(rng, (n_kv[0], hkv, d), "bf16", 0.1), torch.bfloat16) for _ in range(2))

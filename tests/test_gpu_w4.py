@@ -18,15 +18,16 @@ pytestmark = pytest.mark.gpu
 
 @pytest.mark.parametrize("hq,hkv,d,n_kv,n_rows,pad,rot", [
     (32, 8, 128, [200] * 70, [180] * 70, 0, False),               # 70 requests: no ranking by length
-    (32, 8, 128, [64, 63, 65, 1] * 12, [64, 33, 31, 1] * 12, 128, True),
+    (32, 8, 128, [64, 63, 65, 1] * 40, [64, 33, 31, 1] * 40, 128, True),
     (16, 2, 64, [1500, 40, 1300], [1400, 31, 777], 64, False),     # group 8, head size 64
-    (8, 8, 64, [700, 129], [650, 129], 0, True),                   # group 1
+    (8, 8, 64, [700, 129, 690] * 6, [650, 129, 640] * 6, 0, True), # group 1
     (32, 1, 128, [900, 512], [900, 300], 0, True),                 # group 32: 4 rows per block
-    (64, 8, 128, [64] * 40, [64] * 40, 0, False),                  # 64 keys: no workspace
+    (64, 8, 128, [64] * 120, [64] * 120, 0, False),                # 64 keys: no workspace
     (40, 10, 128, [2000], [1700], 128, True),
 ])
 def test_attention_w4(hq, hkv, d, n_kv, n_rows, pad, rot):
     say("attention, 4-wave blocks", hq, hkv, d, len(n_kv), max(n_kv), pad, rot)
+    assert batch_route(n_rows, n_kv, hq, hkv, d) == "w4"
     rng = np.random.default_rng(51)
     cu = lambda x: np.concatenate([[0], np.cumsum(x)]).astype(np.int32)
     cu_kv, cu_r = cu(n_kv), cu(n_rows)
