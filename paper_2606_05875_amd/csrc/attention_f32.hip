@@ -23,6 +23,8 @@
 //    products, into the registers those just freed.
 // 8 x 64 heads over 4 x 128 + 32 keys: 184 rows 224.9 -> 11.5 us, the 32-row
 // probe 33.3 -> 5.1 us (before: one wave per (row, head), one key at a time).
+//  * At head size 128 the fragments, O and the next tiles fill the 256 registers of two waves
+//    per SIMD; 14 (explicit positions) and 8 spill to scratch.
 //  * exp2f, not the bare instruction: weights below 2^-126 stay subnormal numbers (0 to 7%
 //    of a call's time, 2000-key probe of 8/2 heads of 64 63.1 -> 67.5 us).
 // Error against float64, mean of 14 small layers: 2.2e-7 -> 1.5e-7 (rows), 3.3e-7

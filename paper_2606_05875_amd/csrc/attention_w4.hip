@@ -8,7 +8,8 @@
 // ragged batch once per ~44.  Two half-size blocks hide each other's ends, their waves drift
 // out of step by themselves (one's products beside the other's exponentials), and a call has
 // twice as many tiles to even out.  Each tile is loaded by twice as many blocks, which costs
-// one very long request ~2% (its 8-wave blocks with work queues stay).
+// one very long request ~2% (its 8-wave blocks with work queues stay), and a block alone on its
+// CU waits for its keys in every step (batches of few tiles take 8-wave blocks: attn_route).
 // Bound: matrix cores and vector ALUs together.  A wave's step takes ~2600 cycles beside its
 // neighbour's and ~2350 alone (1024 of them products: the two waves of a SIMD keep its matrix
 // core ~78% busy).

@@ -348,9 +348,14 @@ __global__ __launch_bounds__(kW * 64) void scores_pass_bf16(
 // come through a 4-stage LDS ring (64 keys, buffer loads into LDS three stages ahead) instead
 // of registers, which leaves room for both score tiles at two blocks per CU.  Scores and
 // selection at that size 180 -> 170 us, a ragged 16-request batch 322 -> 287 us.  With 128-key
-// stages (one block per CU) 188 and 371 us: nothing hides a block's start.  Shorter splits
-// gain nothing (10 x 512 tokens: 24.9 us either way) and keep the pass above, as do keys
-// rotated on the fly.
+// stages (one block per CU) 188 and 371 us: nothing hides a block's start.  Where the line lies
+// (score calls, us, the pass above / this one, 64/8 heads of 128): 128 query rows, splits of 64
+// keys 26.9 / 28.9, 128 29.2 / 32.2, 192 34.9 / 35.6, 256 39.8 / 41.2, 384 47.6 / 47.1, 512 58.2 /
+// 57.3, 768 74.9 / 73.5; one tile of 64 vectors, 768 keys 40.7 / 36.0, 1056 50.6 / 43.4; 8 requests,
+// 96 keys 67 / 77; head size 64, 128 rows, 256 keys 32.8 / 33.9, 512 46.1 / 44.9.  So splits of 512
+// keys and more; shorter ones keep the pass above, as do keys rotated on the fly.  (Its wait for Q
+// stands inside the loop: moved before it, as here, those calls gain nothing, 39.5 / 39.9 us for
+// 5120 keys rotated on the fly, 62.7 / 65.4 for four requests over 128-key splits.)
 template <int D, bool kCols>
 __global__ __launch_bounds__(kW * 64, 4) void scores_ring_bf16(  // (4 waves per SIMD: two blocks per CU)
     float* __restrict__ part, float* __restrict__ colp, const uint16_t* __restrict__ q,
