@@ -356,13 +356,13 @@ constexpr int kW8Qv = 32 * kW8;       // query vectors per block
 constexpr int kStages = 4;            // LDS ring depth
 
 // Work of an 8-wave block.  Plain mode: block -> (KV head g, request b, row
-// tile), the tile's whole key range (fixed by the block id, or claimed from a
-// work queue for one long request).  Stream mode (few, unequal tiles): a
-// persistent grid of nbg blocks per KV head; the head's work -- every row
-// tile of every request in (request, row tile) order, each counted as
-// kSegCost start-up steps followed by its 64-key steps -- is cut into nbg
-// equal contiguous ranges, one per block, so every block does about the same
-// amount of work whatever the row positions.  A row tile cut by a range
+// tile), the tile's whole key range (kFixed: by the block id; or claimed from a
+// work queue for one long request: both in one kernel cost that request 0.3%).
+// Stream mode (few, unequal tiles): a persistent grid of nbg blocks per KV
+// head; the head's work -- every row tile of every request in (request, row
+// tile) order, each counted as kSegCost start-up steps followed by its 64-key
+// steps -- is cut into nbg equal contiguous ranges, one per block, so every
+// block does about the same amount of work whatever the row positions.  A row tile cut by a range
 // boundary leaves partial results (at most two per block: its first and its
 // last segment) that attn_stream_merge_kernel combines.
 constexpr int kMaxStreamTiles = 256;  // row tiles (requests x tiles) of a stream-mode call
@@ -383,7 +383,7 @@ constexpr int kQueues = 8;
 constexpr int kQueueStride = 32;
 constexpr int kHwRegXccId = (31 << 11) | 20;  // s_getreg: XCC_ID, bits [31:0]
 
-template <int D, bool kStream, bool kRot>
+template <int D, bool kStream, bool kRot, bool kFixed = false>
 __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
     uint16_t* __restrict__ out, float* __restrict__ lse, const uint16_t* __restrict__ q,
     const int32_t* __restrict__ row_pos, int64_t n_rows, const int32_t* __restrict__ cu_rows,
@@ -767,7 +767,7 @@ __global__ __launch_bounds__(kW8 * 64, 1) void attn_w8_kernel(
   if (!kStream) {
     // this block's row tile, all of its keys (up to its largest row position)
     int tile, b = 0;
-    if (queue) {
+    if constexpr (!kFixed) {
       // One long request: the items (row tile, KV head), last row tile (most keys) first, are
       // handed out by counters in the workspace.  Queue j holds the tiles of KV heads j,
       // j + nq, ...; a block takes from the queue of its XCD (whose L2 then serves one
@@ -1290,17 +1290,22 @@ hipError_t launch_sparse_attn(void* out, float* lse, const void* q, const int32_
     }
     if (nblocks > 0x7fffffff) return hipErrorInvalidConfiguration;
     const dim3 grid((unsigned)nblocks);
-#define QCF_W8(D, R)                                                                              \
-  attn_w8_kernel<D, false, R><<<grid, kW8 * 64, 0, stream>>>(                                     \
+#define QCF_W8(D, R, F)                                                                           \
+  attn_w8_kernel<D, false, R, F><<<grid, kW8 * 64, 0, stream>>>(                                  \
       static_cast<uint16_t*>(out), lse, static_cast<const uint16_t*>(q), row_pos, n_rows, cu_rows, \
       static_cast<const uint16_t*>(k_cache), static_cast<const uint16_t*>(v_cache), n_kv_rows,    \
       kv_row_stride, cu_kv, s.batch, max_tiles, s.hkv, s.hq, lg, scale2, 0, nullptr, nullptr,     \
       nullptr, qrot.src, qrot.n_src, rtab, (int)qrot.n_table, queue)
-    if (s.d == 64) {
-      if (rot) QCF_W8(64, true); else QCF_W8(64, false);
-    } else {
-      if (rot) QCF_W8(128, true); else QCF_W8(128, false);
-    }
+#define QCF_W8D(D)                                                                                \
+  do {                                                                                            \
+    if (queue) {                                                                                  \
+      if (rot) QCF_W8(D, true, false); else QCF_W8(D, false, false);                              \
+    } else {                                                                                      \
+      if (rot) QCF_W8(D, true, true); else QCF_W8(D, false, true);                                \
+    }                                                                                             \
+  } while (0)
+    if (s.d == 64) QCF_W8D(64); else QCF_W8D(128);
+#undef QCF_W8D
 #undef QCF_W8
     return hipGetLastError();
   }
