@@ -21,7 +21,7 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kUnits = 2;  // 16-byte units per thread per pass (swept: 1, 2, 4)
 
-template <typename T, int D>
+template <typename T, int D, bool kBig>
 struct AssembleArgs {
   T *k_cache, *v_cache;
   int64_t n_rows, row_stride;
@@ -41,11 +41,11 @@ struct AssembleArgs {
   const int32_t *probe_src, *probe_delta;
   int probe_rows_per_block;
   int hq, hkv;
-  RopeFreq freq;
+  RopeFreq<kBig> freq;
 };
 
-template <typename T, int D, bool kStreamIn>
-__global__ __launch_bounds__(kThreads) void assemble_kernel(AssembleArgs<T, D> A) {
+template <typename T, int D, bool kStreamIn, bool kBig>
+__global__ __launch_bounds__(kThreads) void assemble_kernel(AssembleArgs<T, D, kBig> A) {
   constexpr int HALF = D / 2;
   __shared__ float2 cs[HALF];
   const int n_remap = A.n_seg * A.tiles_per_seg;
@@ -120,9 +120,9 @@ __global__ __launch_bounds__(kThreads) void assemble_kernel(AssembleArgs<T, D> A
   }
 }
 
-template <typename T, int D>
+template <typename T, int D, bool kBig>
 hipError_t assemble_t(const AssembleShape& s, const AssemblePtrs& p, hipStream_t stream) {
-  AssembleArgs<T, D> A;
+  AssembleArgs<T, D, kBig> A;
   A.k_cache = static_cast<T*>(p.k_cache);
   A.v_cache = static_cast<T*>(p.v_cache);
   A.n_rows = s.n_rows;
@@ -159,7 +159,7 @@ hipError_t assemble_t(const AssembleShape& s, const AssemblePtrs& p, hipStream_t
   A.probe_rows_per_block = 1;  // one slot per block: its loads are the only round trip
   A.hq = s.hq;
   A.hkv = s.hkv;
-  A.freq = rope_freq(s.theta, D);
+  A.freq = rope_freq<kBig>(s.theta, D);
   const int64_t n_remap = (int64_t)s.n_seg * A.tiles_per_seg;
   const int64_t n_probe_blocks = (s.n_probe + A.probe_rows_per_block - 1) / A.probe_rows_per_block;
   const int64_t blocks = n_remap + s.n_query + n_probe_blocks;
@@ -168,17 +168,24 @@ hipError_t assemble_t(const AssembleShape& s, const AssemblePtrs& p, hipStream_t
   // the stored chunk caches' K and V bytes
   const int64_t src_bytes = s.n_pic_rows * (int64_t)s.hkv * D * (int64_t)sizeof(T) * 2;
   if (src_bytes > kStreamSourceBytes)
-    assemble_kernel<T, D, true><<<dim3((unsigned)blocks), kThreads, 0, stream>>>(A);
+    assemble_kernel<T, D, true, kBig><<<dim3((unsigned)blocks), kThreads, 0, stream>>>(A);
   else
-    assemble_kernel<T, D, false><<<dim3((unsigned)blocks), kThreads, 0, stream>>>(A);
+    assemble_kernel<T, D, false, kBig><<<dim3((unsigned)blocks), kThreads, 0, stream>>>(A);
   return hipGetLastError();
 }
 
 }  // namespace
 
 hipError_t launch_assemble(const AssembleShape& s, const AssemblePtrs& p, hipStream_t stream) {
-  if (s.bf16) return s.d == 64 ? assemble_t<uint16_t, 64>(s, p, stream) : assemble_t<uint16_t, 128>(s, p, stream);
-  return s.d == 64 ? assemble_t<float, 64>(s, p, stream) : assemble_t<float, 128>(s, p, stream);
+#define QCF_ASSEMBLE(T, D) \
+  return s.theta < kBigTheta ? assemble_t<T, D, true>(s, p, stream) : assemble_t<T, D, false>(s, p, stream)
+  if (s.bf16) {
+    if (s.d == 64) QCF_ASSEMBLE(uint16_t, 64);
+    QCF_ASSEMBLE(uint16_t, 128);
+  }
+  if (s.d == 64) QCF_ASSEMBLE(float, 64);
+  QCF_ASSEMBLE(float, 128);
+#undef QCF_ASSEMBLE
 }
 
 }  // namespace qcf

@@ -70,12 +70,12 @@ struct RopeUnits {
   }
 };
 
-template <typename T, int D>
+template <typename T, int D, bool kBig>
 __global__ __launch_bounds__(kThreads) void scatter_kv_kernel(
     T* k_cache, T* v_cache, int64_t n_cache_rows, int64_t cache_stride, const T* k_new,
     const T* v_new, const T* q_new, T* q_out, int64_t n_src_rows, const int32_t* src_idx,
     const int32_t* __restrict__ row_idx, const int32_t* __restrict__ row_pos, int hq, int hkv,
-    RopeFreq freq) {
+    RopeFreq<kBig> freq) {
   constexpr int HALF = D / 2;
   constexpr int VEC = Vec16<T>::N;
   constexpr int UPH = HALF / VEC;
@@ -121,11 +121,11 @@ __global__ __launch_bounds__(kThreads) void scatter_kv_kernel(
 // the whole row in one round), forms one (cos, sin) pair of the row meanwhile,
 // and stores after the block's table is complete.  Same rotation arithmetic as
 // scatter_kv_kernel, so the same bits.
-template <typename T, int D>
+template <typename T, int D, bool kBig>
 __global__ __launch_bounds__(kThreads) void scatter_kv_rows_kernel(
     T* k_cache, T* v_cache, int64_t n_cache_rows, int64_t cache_stride, const T* k_new,
     const T* v_new, int64_t n_src_rows, const int32_t* src_idx, const int32_t* __restrict__ row_idx,
-    const int32_t* __restrict__ row_pos, int64_t n_rows, int hkv, RopeFreq freq) {
+    const int32_t* __restrict__ row_pos, int64_t n_rows, int hkv, RopeFreq<kBig> freq) {
   constexpr int HALF = D / 2;
   constexpr int VEC = Vec16<T>::N;
   constexpr int UPH = HALF / VEC;
@@ -183,22 +183,23 @@ __global__ __launch_bounds__(kThreads) void scatter_kv_rows_kernel(
   }
 }
 
-template <typename T, int D>
+template <typename T, int D, bool kBig>
 hipError_t scatter_t(void* k_cache, void* v_cache, int64_t n_cache_rows, int64_t cache_stride,
                      const void* k_new, const void* v_new, const void* q_new, void* q_out,
                      int64_t n_src_rows, const int32_t* src_idx, int64_t n_rows,
                      const int32_t* row_idx, const int32_t* row_pos, int hq, int hkv,
                      double theta, hipStream_t stream) {
-  const RopeFreq freq = rope_freq(theta, D);
+  const RopeFreq<kBig> freq = rope_freq<kBig>(theta, D);
   if (!q_new && !q_out) {
     constexpr int RPB = kThreads / 64;
-    scatter_kv_rows_kernel<T, D><<<dim3((unsigned)((n_rows + RPB - 1) / RPB)), kThreads, 0, stream>>>(
+    scatter_kv_rows_kernel<T, D, kBig>
+        <<<dim3((unsigned)((n_rows + RPB - 1) / RPB)), kThreads, 0, stream>>>(
         static_cast<T*>(k_cache), static_cast<T*>(v_cache), n_cache_rows, cache_stride,
         static_cast<const T*>(k_new), static_cast<const T*>(v_new), n_src_rows, src_idx, row_idx,
         row_pos, n_rows, hkv, freq);
     return hipGetLastError();
   }
-  scatter_kv_kernel<T, D><<<dim3((unsigned)n_rows), kThreads, 0, stream>>>(
+  scatter_kv_kernel<T, D, kBig><<<dim3((unsigned)n_rows), kThreads, 0, stream>>>(
       static_cast<T*>(k_cache), static_cast<T*>(v_cache), n_cache_rows, cache_stride,
       static_cast<const T*>(k_new), static_cast<const T*>(v_new), static_cast<const T*>(q_new),
       static_cast<T*>(q_out), n_src_rows, src_idx, row_idx, row_pos, hq, hkv, freq);
@@ -228,10 +229,12 @@ hipError_t launch_scatter_kv(void* k_cache, void* v_cache, int64_t n_cache_rows,
                              const int32_t* row_idx, const int32_t* row_pos, int hq, int hkv,
                              int d, double theta, hipStream_t stream) {
   if (n_rows == 0) return hipSuccess;
-#define QCF_SCATTER(T, D)                                                                   \
-  return scatter_t<T, D>(k_cache, v_cache, n_cache_rows, cache_row_stride, k_new, v_new, q_new, \
-                         q_out, n_src_rows, src_idx, n_rows, row_idx, row_pos, hq, hkv, theta, \
-                         stream)
+  const auto call = [&](auto f) {
+    return f(k_cache, v_cache, n_cache_rows, cache_row_stride, k_new, v_new, q_new, q_out, n_src_rows,
+             src_idx, n_rows, row_idx, row_pos, hq, hkv, theta, stream);
+  };
+#define QCF_SCATTER(T, D) \
+  return theta < kBigTheta ? call(scatter_t<T, D, true>) : call(scatter_t<T, D, false>)
   if (bf16) {
     if (d == 64) QCF_SCATTER(uint16_t, 64);
     QCF_SCATTER(uint16_t, 128);

@@ -70,26 +70,31 @@ __device__ __forceinline__ void st16_nt(void* p, const uint4& v) {
 // Rotary frequencies omega_j = theta^(-2j/d), as the factors theta^(-2^(i+1)/d) of j's bits i
 // (formed on the host once per launch: omega_j is then at most five float64 products, within
 // 1e-15 of the power, where a float64 pow per angle was most of a block's start).
+// kBig: angles of 2^52 and more can occur, which takes theta < kBigTheta (positions are 32-bit).
+constexpr double kBigTheta = 1e-6;
+template <bool kBig>
 struct RopeFreq {
   double f[6];
 };
-inline RopeFreq rope_freq(double theta, int d) {
-  RopeFreq r;
+template <bool kBig>
+inline RopeFreq<kBig> rope_freq(double theta, int d) {
+  RopeFreq<kBig> r;
   for (int i = 0; i < 6; ++i) r.f[i] = pow(theta, -2.0 * (double)(1 << i) / (double)d);
   return r;
 }
 
 // The (cos, sin) of pos * omega_j, formed in float64 and rounded to float32.  The angle is reduced
 // by multiples of pi/2 (two-part constant, one fused multiply-add each: exact to float64 rounding
-// for angles below 2^52; larger ones, which take theta < 1e-6, go through the library) and both
-// functions come from their Taylor series on [-pi/4, pi/4] (first omitted terms below 1e-16).  With the
+// for angles below 2^52; kernels of their own send larger ones through the library, whose code in
+// every kernel cost assembly 0.5%) and both functions come from their Taylor series on [-pi/4, pi/4] (first omitted terms below 1e-16).  With the
 // library's pow and sincos a block's start took longer: assembling a 32K-token request 58.7 ->
 // 56.1 us, a layer recompute of 10 x 512 tokens ~1 us less in each of its two rotations.
-__device__ __forceinline__ float2 rope_cs(double pos, int j, const RopeFreq& fr) {
+template <bool kBig>
+__device__ __forceinline__ float2 rope_cs(double pos, int j, const RopeFreq<kBig>& fr) {
   double x = pos;
 #pragma unroll
   for (int i = 0; i < 6; ++i) x = (j >> i) & 1 ? x * fr.f[i] : x;
-  if (!(fabs(x) < 0x1p52)) {  // (the library's reduction; infinity, NaN: NaN)
+  if (kBig && !(fabs(x) < 0x1p52)) {  // (infinity, NaN: NaN)
     double s, c;
     sincos(x, &s, &c);
     return make_float2((float)c, (float)s);

@@ -19,13 +19,13 @@ namespace {
 constexpr int kThreads = 256;
 constexpr int kUnitsPerThread = 1;  // key units (rotate-half pairs) per thread per round (swept: 1, 2, 4)
 
-template <typename T, int D, bool kStreamIn>
+template <typename T, int D, bool kStreamIn, bool kBig>
 __global__ __launch_bounds__(kThreads) void rerope_kernel(
     T* k_out, const T* k_in, T* v_out, const T* v_in, int64_t n_out_rows, int64_t n_in_rows,
     int hkv, int64_t out_stride, int64_t in_stride, int rows_per_block,
     const int32_t* __restrict__ seg_start,
     const int32_t* __restrict__ seg_len, const int32_t* __restrict__ seg_delta,
-    const int32_t* __restrict__ src_start, RopeFreq freq) {
+    const int32_t* __restrict__ src_start, RopeFreq<kBig> freq) {
   constexpr int HALF = D / 2;
   __shared__ float2 cs[HALF];
 
@@ -45,7 +45,7 @@ __global__ __launch_bounds__(kThreads) void rerope_kernel(
       });
 }
 
-template <typename T, int D>
+template <typename T, int D, bool kBig>
 hipError_t launch_t(void* k_out, const void* k_in, void* v_out, const void* v_in,
                     int64_t n_out_rows, int64_t n_in_rows, int hkv, int64_t out_stride,
                     int64_t in_stride, int n_seg,
@@ -57,19 +57,21 @@ hipError_t launch_t(void* k_out, const void* k_in, void* v_out, const void* v_in
   // the stored keys' (and values') bytes
   const int64_t src_bytes =
       n_in_rows * (int64_t)hkv * D * (int64_t)sizeof(T) * (v_in != nullptr && v_out != nullptr ? 2 : 1);
-  auto kern = src_bytes > kStreamSourceBytes ? rerope_kernel<T, D, true> : rerope_kernel<T, D, false>;
+  auto kern = src_bytes > kStreamSourceBytes ? rerope_kernel<T, D, true, kBig>
+                                             : rerope_kernel<T, D, false, kBig>;
   kern<<<grid, kThreads, 0, stream>>>(
       static_cast<T*>(k_out), static_cast<const T*>(k_in), static_cast<T*>(v_out),
       static_cast<const T*>(v_in), n_out_rows, n_in_rows, hkv, out_stride, in_stride, rpb, seg_start,
-      seg_len, seg_delta, src_start, rope_freq(theta, D));
+      seg_len, seg_delta, src_start, rope_freq<kBig>(theta, D));
   return hipGetLastError();
 }
 
 // table[i * d/2 + j] = the (cos, sin) that every rotation of this library
 // forms for offset pos[i] and frequency j (float64 angle, rounded to float32)
+template <bool kBig>
 __global__ __launch_bounds__(64) void rope_table_kernel(float2* __restrict__ table,
                                                         const int32_t* __restrict__ pos, int d,
-                                                        RopeFreq freq) {
+                                                        RopeFreq<kBig> freq) {
   const int64_t i = blockIdx.x;
   if ((int)threadIdx.x < d / 2)
     table[i * (d / 2) + threadIdx.x] = rope_cs((double)pos[i], threadIdx.x, freq);
@@ -80,8 +82,12 @@ __global__ __launch_bounds__(64) void rope_table_kernel(float2* __restrict__ tab
 hipError_t launch_rope_table(float* table, const int32_t* pos, int64_t n, int d, double theta,
                              hipStream_t stream) {
   if (n == 0) return hipSuccess;
-  rope_table_kernel<<<dim3((unsigned)n), 64, 0, stream>>>(reinterpret_cast<float2*>(table), pos, d,
-                                                          rope_freq(theta, d));
+  float2* t = reinterpret_cast<float2*>(table);
+  const dim3 grid((unsigned)n);
+  if (theta < kBigTheta)
+    rope_table_kernel<<<grid, 64, 0, stream>>>(t, pos, d, rope_freq<true>(theta, d));
+  else
+    rope_table_kernel<<<grid, 64, 0, stream>>>(t, pos, d, rope_freq<false>(theta, d));
   return hipGetLastError();
 }
 
@@ -93,10 +99,11 @@ hipError_t launch_rerope(void* k_out, const void* k_in, void* v_out, const void*
                          const int32_t* src_start, int max_seg_len, double theta,
                          hipStream_t stream) {
   if (n_seg == 0 || max_seg_len == 0 || n_out_rows == 0 || n_in_rows == 0) return hipSuccess;
-#define QCF_REROPE(T, D)                                                                       \
-  return launch_t<T, D>(k_out, k_in, v_out, v_in, n_out_rows, n_in_rows, hkv, out_row_stride,   \
-                        in_row_stride, n_seg,                                                  \
-                        seg_start, seg_len, seg_delta, src_start, max_seg_len, theta, stream)
+  const auto call = [&](auto f) {
+    return f(k_out, k_in, v_out, v_in, n_out_rows, n_in_rows, hkv, out_row_stride, in_row_stride, n_seg,
+             seg_start, seg_len, seg_delta, src_start, max_seg_len, theta, stream);
+  };
+#define QCF_REROPE(T, D) return theta < kBigTheta ? call(launch_t<T, D, true>) : call(launch_t<T, D, false>)
   if (bf16) {
     if (d == 64) QCF_REROPE(uint16_t, 64);
     QCF_REROPE(uint16_t, 128);

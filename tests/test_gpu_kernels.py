@@ -357,6 +357,38 @@ def test_rope_table_large_angles(d):
         assert np.abs(table.double().cpu().numpy() - want).max() < tol
 
 
+@pytest.mark.parametrize("dtype,d", [("bf16", 64), ("bf16", 128), ("f32", 64), ("f32", 128)])
+def test_rotations_by_large_angles(dtype, d):
+    """Every kernel that rotates turns by angles of 2^52 and more (theta = 2^-64) as the oracle does."""
+    say("rotations by large angles", dtype, d)
+    rng = np.random.default_rng(12)
+    hq, hkv, n, theta = 4, 2, 40, 2.0 ** -64
+    dt, i32 = DT[dtype], lambda a: dev(np.asarray(a, np.int32))
+    k, v = draw(rng, (n, hkv, d), dtype), draw(rng, (n, hkv, d), dtype)
+    q = draw(rng, (n, hq, d), dtype)
+    pos = rng.integers(0, 2 ** 31, n).astype(np.int32)
+    want = {x: Q.round_storage(Q.rope(a, pos, theta), dtype) for x, a in (("k", k), ("q", q))}
+    kt, vt, qt = dev(k, dt), dev(v, dt), dev(q, dt)
+    new = lambda h: torch.zeros((n, h, d), dtype=dt, device="cuda")
+    rows, ones = i32(np.arange(n)), i32(np.ones(n))
+    out = {}
+    qcf.qcf_rerope(out.setdefault("rerope", new(hkv)), kt, rows, ones, dev(pos), 1, theta)
+    qcf.qcf_scatter_kv(out.setdefault("scatter", new(hkv)), new(hkv), kt, vt, rows, dev(pos), theta)
+    q_out = new(hq)
+    qcf.qcf_scatter_kv(out.setdefault("scatter with q", new(hkv)), new(hkv), kt, vt, rows, dev(pos), theta,
+                       q_new=qt, q_out=q_out)
+    # the first half as segments, the second as query rows; the probe buffer takes the segments' rows
+    h, q_u, pk, pv = n // 2, torch.zeros((n // 2, hq, d), dtype=dt, device="cuda"), new(hkv)[:n // 2], new(hkv)[:n // 2]
+    qcf.qcf_assemble(out.setdefault("assemble", new(hkv)), new(hkv), kt, vt, rows[:h], ones[:h], dev(pos[:h]), 1,
+                     qt, kt, vt, rows[h:], dev(pos[h:]), q_u, pk, pv, rows[:h], dev(pos[:h]), theta,
+                     query_src=rows[h:])
+    for name, x in out.items():
+        assert_ulp(host(x), want["k"], dtype, name)
+    assert_ulp(host(pk), want["k"][:h], dtype, "probe buffer")
+    assert_ulp(host(q_out), want["q"], dtype, "scattered queries")
+    assert_ulp(host(q_u), want["q"][h:], dtype, "assembled queries")
+
+
 @pytest.mark.parametrize("dtype,nqs,ctxs,hq,hkv,d,pad", [
     ("bf16", [64], [5120], 32, 8, 128, 128),            # 10 x 512-token chunks, padded rows
     ("bf16", [17, 1, 128], [700, 3000, 129], 32, 8, 128, 0),
